@@ -661,11 +661,16 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
     if (e == hipSuccess) e = dalloc(&nl->lenA, Nn);
     if (e == hipSuccess) e = dalloc(&nl->offA, Nn * (kMaxSpecies + 1));
     if (e == hipSuccess) e = dalloc(&nl->revA, Nn * capA);
-    if (e == hipSuccess) e = dalloc(&nl->uniR, Nn * capR);
-    if (e == hipSuccess) e = dalloc(&nl->umR, Nn * capR);
-    if (e == hipSuccess) e = dalloc(&nl->umA, Nn * capA);
+    // The force kernels read list entries in batches that may run past a
+    // block, into other valid entries: the arrays start out as zeros (every
+    // entry a valid index) and end in slack, a batch past the last row and,
+    // in the angular force, the longest block of a wavefront more.
+    const size_t slack = (size_t)capA + 16;
+    if (e == hipSuccess) e = dalloc(&nl->uniR, Nn * capR + slack);
+    if (e == hipSuccess) e = dalloc(&nl->umR, Nn * capR + slack);
+    if (e == hipSuccess) e = dalloc(&nl->umA, Nn * capA + slack);
     if (e == hipSuccess) e = dalloc(&nl->uendR, Nn * kMaxSpecies);
-    if (e == hipSuccess) e = dalloc(&nl->uniA, Nn * capA);
+    if (e == hipSuccess) e = dalloc(&nl->uniA, Nn * capA + slack);
     if (e == hipSuccess) e = dalloc(&nl->uendA, Nn * kMaxSpecies);
     if (e == hipSuccess) e = dalloc(&nl->pairbuf, 4 * PN * capA);
     if (e == hipSuccess) e = dalloc(&nl->pos4, 4 * PN);
@@ -673,6 +678,12 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
     if (e == hipSuccess) e = dalloc(&nl->grid, 16 + kDevSysWords * (size_t)nsys);
     if (e == hipSuccess) e = dalloc(&nl->status, 8);
     if (e == hipSuccess) e = hipMemset(nl->status, 0, 8 * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMemset(nl->uniR, 0, sizeof(int32_t) * (Nn * capR + slack));
+    if (e == hipSuccess) e = hipMemset(nl->uniA, 0, sizeof(int32_t) * (Nn * capA + slack));
+    if (e == hipSuccess) e = hipMemset(nl->umR, 0, sizeof(uint64_t) * (Nn * capR + slack));
+    if (e == hipSuccess) e = hipMemset(nl->umA, 0, sizeof(uint64_t) * (Nn * capA + slack));
+    if (e == hipSuccess && Nn) e = hipMemset(nl->candA, 0, sizeof(int32_t) * Nn * capA);
+    if (e == hipSuccess && Nn) e = hipMemset(nl->revA, 0, sizeof(int32_t) * Nn * capA);
     // pair terms start at zero: a slot that a step with truncated rows leaves
     // unwritten then holds a finite stale value, never uninitialised bits
     if (e == hipSuccess && PN) e = hipMemset(nl->pairbuf, 0, sizeof(float) * 4 * PN * capA);

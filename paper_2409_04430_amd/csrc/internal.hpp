@@ -80,11 +80,19 @@ __host__ __device__ inline MlpFrag mlp_frag_layout(int D, int H, int wt)
 }  // namespace nep
 
 namespace nep {
+// Form of a system's packed positions: fixed point (orthorhombic cells with
+// edges up to kFixedMaxEdge), or the fine grid of an orthorhombic or a
+// general cell.  A system's form depends on its own cell alone, so its
+// results do not depend on the batch it is in.
+enum PosForm { kPosFixed = 0, kPosGrid = 1, kPosGridTri = 2 };
+
 // Geometry of one system of a batch (device copy in the list handle).
 struct SysGeom {
     double L[3], invL[3];     // orthorhombic box edges (triclinic: the diagonal of H, unused)
     double hd[3], Minv[3];    // fine grid spacing and M / L (packing, orthorhombic)
     float h[3];               // fine grid spacing (FP32, pair vectors, orthorhombic)
+    float fx[6];              // L / 2^32, the quantum of fixed-point positions, as two FP32 terms: high [3], low [3]
+    int form;                 // packed positions of this system: kPosFixed, kPosGrid or kPosGridTri
     int M[3];                 // fine grid cells per axis (along the cell's edge vectors)
     int nc_cap[3];            // cell-list allocation bound per axis
     int cell_base;            // first global cell of the system
@@ -121,6 +129,7 @@ struct nep_nlist {
     std::vector<double> boxL;     // host [nsys][9] cells of the last build (0: none yet)
     float margin = 0.0f;          // FP32 pre-test margin of the last build's geometry
     int any_tri = 0;              // some system of the last build has a general (triclinic) cell
+    int fine_pos = 0;             // some system of the last build has fine-grid positions (not kPosFixed)
     nep::SysGeom *geom = nullptr; // [nsys]
     int32_t *atom_sys = nullptr;  // [N]
     int32_t *cell_sys = nullptr;  // [ncell_alloc]
@@ -268,7 +277,7 @@ __device__ __forceinline__ void reduce_output(const PendingReduce &r, int o, int
 // Orthorhombic edge lengths from a row-vector cell; false if not orthorhombic.
 bool box_lengths(const double box[9], double L[3]);
 
-// Packed positions: per axis a fine grid of M cells of width h = L / M; a
+// Packed positions on a fine grid: per axis a fine grid of M cells of width h = L / M; a
 // bead position is stored as FP32 offsets inside its cell plus the three
 // cell indices (10 bits each) in the w word.  h <= 1 A and h <= (L/2 - rc)/2,
 // so every pair closer than rc takes its minimum image from the integer cell
@@ -286,7 +295,49 @@ FineGrid fine_grid(const double L[3], double rc);
 FineGrid fine_grid_cell(const CellInfo &c, double rc);
 
 
-// One packed position: per axis the fine cell c = floor(x / h) mod M
+// Fixed-point positions (kPosFixed): per axis the fractional coordinate as a 32-bit
+// integer, so that the wrapped integer difference of two atoms is their
+// minimum image and a pair vector costs 12 instructions (subtraction,
+// conversion, product and its correction per axis) against 24 for the fine
+// grid below, of about 70 per pair in the descriptor's radial loop.  The
+// quantum enters as two FP32 terms: rounded to one, all distances along an
+// axis would carry the same relative error (up to 6e-8, a strain), which
+// the virial of a near-equilibrium crystal magnifies.  The quantum L / 2^32
+// is at most 6e-8 A at the largest edge, the FP32 rounding of the fine
+// grid's offsets; longer edges and general cells keep the fine grid.
+constexpr double kFixedMaxEdge = 256.0;
+
+// Fixed-point form of one position: integers in x, y, z, and in w 0, or NaN
+// for a non-finite position (added in the list build's pre-test, which then
+// falls through to the exact test).
+__device__ __forceinline__ float4 pack_fixed(const double *x3, const SysGeom &g)
+{
+    uint32_t q[3];
+    bool fin = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double u = x3[d] * g.invL[d];
+        fin = fin && isfinite(x3[d]);
+        const double r = rint((u - floor(u)) * 4294967296.0);
+        q[d] = r >= 0.0 && r < 4294967296.0 ? (uint32_t)r : 0u;   // 2^32 wraps to 0
+    }
+    return make_float4(__uint_as_float(q[0]), __uint_as_float(q[1]), __uint_as_float(q[2]),
+                       fin ? 0.0f : __int_as_float(0x7fc00000));
+}
+
+// r_j - r_i from fixed-point positions (exact minimum image for |r| < L / 2).
+__device__ __forceinline__ void fixed_pair(const float4 &pj, const float4 &pi, const float fx[6], float &dx, float &dy,
+                                           float &dz)
+{
+    const float cx = (float)(int32_t)(__float_as_uint(pj.x) - __float_as_uint(pi.x));
+    const float cy = (float)(int32_t)(__float_as_uint(pj.y) - __float_as_uint(pi.y));
+    const float cz = (float)(int32_t)(__float_as_uint(pj.z) - __float_as_uint(pi.z));
+    dx = fmaf(cx, fx[0], cx * fx[3]);
+    dy = fmaf(cy, fx[1], cy * fx[4]);
+    dz = fmaf(cz, fx[2], cz * fx[5]);
+}
+
+// One packed position on the fine grid: per axis the fine cell c = floor(x / h) mod M
 // (10 bits per axis in w; unwrapped coordinates allowed) and the FP32
 // offset x - floor(x / h) h inside it; a non-finite coordinate gives a NaN
 // offset.
@@ -317,7 +368,8 @@ __device__ __forceinline__ float4 pack_one_tri(const double *x3, const SysGeom &
 
 __device__ __forceinline__ float4 pack_one(const double *x3, const SysGeom &g)
 {
-    if (g.tri) return pack_one_tri(x3, g);
+    if (g.form == kPosFixed) return pack_fixed(x3, g);
+    if (g.form == kPosGridTri) return pack_one_tri(x3, g);
     float o[3];
     int bits = 0;
     bool fin = true;
@@ -494,12 +546,26 @@ __device__ __forceinline__ bool pair_within(float r2f, const CutTest &c, const d
     return (tri ? mic_r2_exact_tri(ri, rj, g.H, g.G) : mic_r2_exact(ri, rj, g.L, g.invL)) < c.rc2;
 }
 
-// r_j - r_i from packed positions of the system's fine grid (tri as for mic_vec).
-__device__ __forceinline__ void packed_pair_g(const float4 &pj, const float4 &pi, const SysGeom &g, bool tri,
-                                              float &dx, float &dy, float &dz)
+// r_j - r_i from packed positions.  FINE = false: every system of the launch
+// has fixed-point positions (no code of the other forms).
+template <bool FINE>
+__device__ __forceinline__ void packed_pair_g(const float4 &pj, const float4 &pi, const SysGeom &g, float &dx,
+                                              float &dy, float &dz)
 {
-    if (tri) packed_pair_tri(pj, pi, g.M, g.hv, dx, dy, dz);
+    if (!FINE || g.form == kPosFixed) fixed_pair(pj, pi, g.fx, dx, dy, dz);
+    else if (g.form == kPosGridTri) packed_pair_tri(pj, pi, g.M, g.hv, dx, dy, dz);
     else packed_pair(pj, pi, g.M, g.h, dx, dy, dz);
+}
+
+// The squared distance of a packed pair for the cutoff pre-test: NaN where
+// a position is not finite (fixed-point positions carry the NaN in w).
+template <bool FINE>
+__device__ __forceinline__ float packed_r2(const float4 &pj, const float4 &pi, const SysGeom &g)
+{
+    float dx, dy, dz;
+    packed_pair_g<FINE>(pj, pi, g, dx, dy, dz);
+    const float r2 = dx * dx + dy * dy + dz * dz;
+    return !FINE || g.form == kPosFixed ? r2 + (pj.w + pi.w) : r2;
 }
 
 // Lanes per atom: the beads of one atom occupy G = 2^lg consecutive lanes of

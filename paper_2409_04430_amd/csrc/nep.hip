@@ -243,7 +243,7 @@ constexpr int kNetRowRegs = 40;   // longest descriptor whose weight rows the LD
 
 // ----------------------------------------------------------- pass 1 ---
 
-template <int NR1, int NA1, int KR1, int KA1, bool FOUR, int NET, bool TRI>
+template <int NR1, int NA1, int KR1, int KA1, bool FOUR, int NET, bool FINE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_descriptor(NepArgs a, const float *__restrict__ prm)
 {
@@ -259,8 +259,10 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
     const bool valid = lm.valid;
     const int ti = a.types[i];
     const bool tok = ti >= 0 && ti < S;
-    const float4 *p4 = a.p4;
-    const float4 pi = p4[(size_t)i * P + b];
+    const float4 *p4b = a.p4 + b;   // this lane's bead of every atom
+    const uint32_t pstride = (uint32_t)P * sizeof(float4);
+    const uint64_t bit = 1ull << b;
+    const float4 pi = *row_at(p4b, i, pstride);
     const float *shc = prm + a.osh;
     float U = 0.0f;
 
@@ -311,28 +313,23 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
 #pragma unroll
             for (int k = 0; k < KR1; ++k) sk[k] = 0.0f;
             for (int sb = s0; sb < s1; sb += kBatchR) {
-                int jj[kBatchR];
                 bool in[kBatchR];
                 float4 pj[kBatchR];
-                // every load unconditional (slots past the block end reread
-                // its last entry, masked off) so that the batch's loads are
-                // in flight together
+                // every load unconditional (entries past the block end are
+                // masked off) so that the batch's loads are in flight together
+                const idx_run<kBatchR> jj = *reinterpret_cast<const idx_run<kBatchR> *>(uR + sb);
+                const mask_run<kBatchR> mm = *reinterpret_cast<const mask_run<kBatchR> *>(mR + sb);
 #pragma unroll
-                for (int u = 0; u < kBatchR; ++u) {
-                    const int su = min(sb + u, s1 - 1);
-                    jj[u] = uR[su];
-                    const uint64_t mu = mR[su];
-                    in[u] = (sb + u < s1) & (((mu >> b) & 1u) != 0);
-                }
+                for (int u = 0; u < kBatchR; ++u) in[u] = (sb + u < s1) & ((mm.v[u] & bit) != 0);
 #pragma unroll
-                for (int u = 0; u < kBatchR; ++u) pj[u] = p4[(size_t)jj[u] * P + b];
+                for (int u = 0; u < kBatchR; ++u) pj[u] = *row_at(p4b, jj.v[u], pstride);
 #pragma unroll
                 for (int u = 0; u < kBatchR; ++u) keep(pj[u]);
 #pragma unroll
                 for (int u = 0; u < kBatchR; ++u) {
                     if (in[u]) {
                         float dx, dy, dz;
-                        pair_vec<TRI>(pj[u], pi, lm, dx, dy, dz);
+                        pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
                         const float r2 = dx * dx + dy * dy + dz * dz;
                         {
                             // sk[0] collects f_c, sk[k > 0] collects f_c T_k
@@ -390,32 +387,29 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                 cs[g] = acc;
             }
             // batches of kBatch entries: slots, then partners, then their
-            // positions, each level's loads in flight together (slots past
-            // the block end reread its last entry, masked off)
+            // positions, each level's loads in flight together (entries past
+            // the block end masked off)
             for (int sb = s0; sb < s1; sb += kBatch) {
                 // coefficients through scalar loads, which do not wait on the gathers
                 const cf32p cl = launder(c);
                 int kq[kBatch];
                 bool in[kBatch];
                 float4 pj[kBatch];
+                const idx_run<kBatch> ku = *reinterpret_cast<const idx_run<kBatch> *>(uA + sb);
+                const mask_run<kBatch> mm = *reinterpret_cast<const mask_run<kBatch> *>(mA + sb);
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int su = min(sb + u, s1 - 1);
-                    kq[u] = uA[su];
-                    const uint64_t mu = mA[su];
-                    in[u] = (sb + u < s1) & (((mu >> b) & 1u) != 0);
-                }
+                for (int u = 0; u < kBatch; ++u) in[u] = (sb + u < s1) & ((mm.v[u] & bit) != 0);
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) kq[u] = rowA[kq[u]] >> 2;
+                for (int u = 0; u < kBatch; ++u) kq[u] = rowA[(uint32_t)ku.v[u]] >> 2;
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) pj[u] = p4[(size_t)kq[u] * P + b];
+                for (int u = 0; u < kBatch; ++u) pj[u] = *row_at(p4b, kq[u], pstride);
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) keep(pj[u]);
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
                     if (!in[u]) continue;
                     float dx, dy, dz;
-                    pair_vec<TRI>(pj[u], pi, lm, dx, dy, dz);
+                    pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
                     const float r2 = dx * dx + dy * dy + dz * dz;
                     const float rinv = __builtin_amdgcn_rsqf(r2);
                     const float r = r2 * rinv;
@@ -658,18 +652,20 @@ constexpr int kBatchAng = 4;   // angular entries whose loads are issued togethe
 template <int NA1> constexpr int kAngWaves() { return NA1 > 5 ? 1 : 2; }
 constexpr int kBatchRev = 8;   // reverse angular terms read together by the radial force kernel
 
-template <int NA1, int KA1, bool FOUR, bool PARKED, bool TRI>
+template <int NA1, int KA1, bool FOUR, bool PARKED, bool FINE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAngWaves<NA1>())))
 void k_force_ang(NepArgs a, const float *__restrict__ prm)
 {
     const LaneMap lm = lane_map(a);
     const int i = lm.i, b = lm.b, P = a.P, S = a.S;
     const bool valid = lm.valid;
-    const int ii = i;
     const int ti = a.types[i];
     const bool tok = ti >= 0 && ti < S;
-    const float4 *p4 = a.p4;
-    const float4 pi = p4[(size_t)i * P + b];
+    const float4 *p4b = a.p4 + b;
+    const uint32_t pstride = (uint32_t)P * sizeof(float4);
+    const uint64_t bit = 1ull << b;
+    float4 *pairb = a.pairbuf + b;
+    const float4 pi = *row_at(p4b, i, pstride);
     const float *shc = prm + a.osh;
     const int32_t *uA = a.uniA + (size_t)i * a.capA;
     const uint64_t *mA = a.umA + (size_t)i * a.capA;
@@ -730,28 +726,24 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
             const float *cij = prm + a.oA + (tc * S + t) * NA1 * KA1;
             for (int sb = 0; sb < cmax; sb += kBatchAng) {
                 // the batch's slots, partners, positions and reverse slots,
-                // each level's loads in flight together: every index is
-                // clamped into the row (a lane with an empty block reads its
-                // row's first entry) and its value selected after the load
-                int kq[kBatchAng], jq[kBatchAng], rq[kBatchAng];
+                // each level's loads in flight together (a lane past the end
+                // of its block reads entries that are valid but masked off;
+                // its position stays below the longest block of the
+                // wavefront, which the arrays' slack covers)
+                int jq[kBatchAng], rq[kBatchAng];
                 bool aq[kBatchAng];
                 float4 pq[kBatchAng];
+                const idx_run<kBatchAng> ku = *reinterpret_cast<const idx_run<kBatchAng> *>(uA + s0 + sb);
+                const mask_run<kBatchAng> mm = *reinterpret_cast<const mask_run<kBatchAng> *>(mA + s0 + sb);
+#pragma unroll
+                for (int u = 0; u < kBatchAng; ++u) aq[u] = (sb + u < cnt) & ((mm.v[u] & bit) != 0);
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) {
-                    const int su = min(s0 + max(min(sb + u, cnt - 1), 0), a.capA - 1);
-                    const int k0 = uA[su];
-                    const uint64_t mu = mA[su];
-                    kq[u] = cnt > 0 ? k0 : 0;
-                    aq[u] = (sb + u < cnt) & (((mu >> b) & 1u) != 0);
+                    jq[u] = rowA[(uint32_t)ku.v[u]] >> 2;
+                    rq[u] = rvA[(uint32_t)ku.v[u]];
                 }
 #pragma unroll
-                for (int u = 0; u < kBatchAng; ++u) {
-                    const int r0 = rowA[kq[u]];
-                    rq[u] = rvA[kq[u]];
-                    jq[u] = cnt > 0 ? (r0 >> 2) : i;
-                }
-#pragma unroll
-                for (int u = 0; u < kBatchAng; ++u) pq[u] = p4[(size_t)jq[u] * P + b];
+                for (int u = 0; u < kBatchAng; ++u) pq[u] = *row_at(p4b, jq[u], pstride);
                 if (!formed) get_adjoints();
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) keep(pq[u]);
@@ -762,7 +754,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                 const bool act = aq[u];
                 if (__ballot(act) == 0) continue;
                 float dx, dy, dz;
-                pair_vec<TRI>(pq[u], pi, lm, dx, dy, dz);
+                pair_vec<FINE>(pq[u], pi, lm, dx, dy, dz);
                 if (!act) {
                     dx = 1.0f;
                     dy = 0.0f;
@@ -800,7 +792,9 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                 const float pz = sY * uz + (gz - uz * ug) * rinv;
                 if (act) {
                     const int rk = rq[u];
-                    if (rk >= 0) a.pairbuf[((size_t)j * a.capA + rk) * P + b] = make_float4(px, py, pz, 0.0f);
+                    if (rk >= 0)
+                        *const_cast<float4 *>(row_at(row_at(pairb, j, (uint32_t)a.capA * pstride), rk, pstride)) =
+                            make_float4(px, py, pz, 0.0f);
                     Fx += px; Fy += py; Fz += pz;
                     Wv[0] = fmaf(-dx, px, Wv[0]); Wv[1] = fmaf(-dx, py, Wv[1]); Wv[2] = fmaf(-dx, pz, Wv[2]);
                     Wv[3] = fmaf(-dy, px, Wv[3]); Wv[4] = fmaf(-dy, py, Wv[4]); Wv[5] = fmaf(-dy, pz, Wv[5]);
@@ -836,7 +830,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
 // bead-minor), then the reverse angular terms -dU_j/dr_ji that the angular
 // pass deposited at this atom's slots, then the angular own part.  Force and
 // per-atom virial sums are kept in FP64.
-template <int KR1, bool TRI>
+template <int KR1, bool FINE>
 __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
 {
     const LaneMap lm = lane_map(a);
@@ -844,8 +838,10 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
     const bool valid = lm.valid;
     const int ti = a.types[i];
     const bool tok = ti >= 0 && ti < S;
-    const float4 *p4 = a.p4;
-    const float4 pi = p4[(size_t)i * P + b];
+    const float4 *p4b = a.p4 + b;
+    const uint32_t pstride = (uint32_t)P * sizeof(float4);
+    const uint64_t bit = 1ull << b;
+    const float4 pi = *row_at(p4b, i, pstride);
     double Fx = 0.0, Fy = 0.0, Fz = 0.0;
     float Wf[9];   // radial pair virial of this (atom, bead), FP32 (a sum of like-signed terms)
 #pragma unroll
@@ -854,8 +850,12 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
 #pragma unroll
     for (int e = 0; e < 9; ++e) Wa[e] = 0.0f;
     if (valid && tok) {
-        auto load_a = [&](int atom, int sp, float *out) {
-            const float4 *p = reinterpret_cast<const float4 *>(a.arad + (((size_t)atom * S + sp) * P + b) * kRadPad);
+        // adjoint rows of this lane's bead: atom j's for species t at j * astride + t * P rows
+        const float *ab = a.arad + (size_t)b * kRadPad;
+        const uint32_t trow = (uint32_t)P * kRadPad * sizeof(float), astride = (uint32_t)S * trow;
+        const float *abt = row_at(ab, ti, trow);
+        auto load_a = [&](const float *row, float *out) {
+            const float4 *p = reinterpret_cast<const float4 *>(row);
 #pragma unroll
             for (int q4 = 0; q4 < kRadPad / 4; ++q4) {
                 const float4 v = p[q4];
@@ -871,24 +871,20 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
             int s0, s1;
             block_range(a.uendR, i, t, s0, s1);
             float ai[KR1 + 1];   // a_k and, last, their sum over k >= 1
-            load_a(i, t, ai);
+            load_a(row_at(row_at(ab, t, trow), i, astride), ai);
             for (int sb = s0; sb < s1; sb += kBatch) {
-                int jj[kBatch];
                 bool in[kBatch];
                 float4 pj[kBatch];
                 float aj[kBatch][KR1 + 1];
                 // unconditional loads, as in the descriptor's radial batches
+                const idx_run<kBatch> jj = *reinterpret_cast<const idx_run<kBatch> *>(uR + sb);
+                const mask_run<kBatch> mm = *reinterpret_cast<const mask_run<kBatch> *>(mR + sb);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) in[u] = (sb + u < s1) & ((mm.v[u] & bit) != 0);
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
-                    const int su = min(sb + u, s1 - 1);
-                    jj[u] = uR[su];
-                    const uint64_t mu = mR[su];
-                    in[u] = (sb + u < s1) & (((mu >> b) & 1u) != 0);
-                }
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    pj[u] = p4[(size_t)jj[u] * P + b];
-                    load_a(jj[u], ti, aj[u]);
+                    pj[u] = *row_at(p4b, jj.v[u], pstride);
+                    load_a(row_at(abt, jj.v[u], astride), aj[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) keep(pj[u]);
@@ -897,7 +893,7 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
                 for (int u = 0; u < kBatch; ++u) {
                     if (in[u]) {
                         float dx, dy, dz;
-                        pair_vec<TRI>(pj[u], pi, lm, dx, dy, dz);
+                        pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
                         const float r2 = dx * dx + dy * dy + dz * dz;
                         const float rinv = __builtin_amdgcn_rsqf(r2);
                         const float r = r2 * rinv;
@@ -934,24 +930,19 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
         const int32_t *uA = a.uniA + (size_t)i * a.capA;
         const uint64_t *mA = a.umA + (size_t)i * a.capA;
         const int32_t *rowA = a.candA + (size_t)i * a.capA;
-        const float4 *pbuf = a.pairbuf + (size_t)i * a.capA * P + b;
+        const float4 *pbuf = row_at(a.pairbuf + b, i, (uint32_t)a.capA * pstride);
         const int nA = a.uendA[(size_t)i * kMaxSpecies + S - 1];
         float gx = 0.0f, gy = 0.0f, gz = 0.0f;
         for (int sb = 0; sb < nA; sb += kBatchRev) {
-            int kk[kBatchRev];
             bool in[kBatchRev];
             float4 d[kBatchRev];
-            // unconditional loads (slots past the list end reread its last
-            // entry; values outside the bead mask are dropped)
+            // unconditional loads (values past the list end or outside the bead mask are dropped)
+            const idx_run<kBatchRev> kk = *reinterpret_cast<const idx_run<kBatchRev> *>(uA + sb);
+            const mask_run<kBatchRev> mm = *reinterpret_cast<const mask_run<kBatchRev> *>(mA + sb);
 #pragma unroll
-            for (int u = 0; u < kBatchRev; ++u) {
-                const int su = min(sb + u, nA - 1);
-                kk[u] = uA[su];
-                const uint64_t mu = mA[su];
-                in[u] = (sb + u < nA) & (((mu >> b) & 1u) != 0);
-            }
+            for (int u = 0; u < kBatchRev; ++u) in[u] = (sb + u < nA) & ((mm.v[u] & bit) != 0);
 #pragma unroll
-            for (int u = 0; u < kBatchRev; ++u) d[u] = pbuf[(size_t)kk[u] * P];
+            for (int u = 0; u < kBatchRev; ++u) d[u] = *row_at(pbuf, kk.v[u], pstride);
 #pragma unroll
             for (int u = 0; u < kBatchRev; ++u) {
                 keep(d[u]);
@@ -966,7 +957,7 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
                 for (int u = 0; u < kBatchRev; ++u) {
                     if (!in[u]) continue;
                     float dx, dy, dz;
-                    pair_vec<TRI>(p4[(size_t)(rowA[kk[u]] >> 2) * P + b], pi, lm, dx, dy, dz);
+                    pair_vec<FINE>(*row_at(p4b, rowA[(uint32_t)kk.v[u]] >> 2, pstride), pi, lm, dx, dy, dz);
                     const float4 dd = d[u];
                     // reverse half of the per-atom split: +1/2 r_ij (x) dU_j/dr_ji
                     const float hx = 0.5f * dx, hy = 0.5f * dy, hz = 0.5f * dz;
@@ -1012,7 +1003,7 @@ __global__ __launch_bounds__(64) void k_reduce(PendingReduce r)
 constexpr size_t kNetLdsMax = 60 * 1024;   // bytes of LDS for the staged network weights
 
 // mlp: NEP_MLP_FP32 (vector units), NEP_MLP_BF16_MFMA or NEP_MLP_FP32_MFMA (matrix cores).
-template <int NR1, int NA1, bool FOUR, bool TRI>
+template <int NR1, int NA1, bool FOUR, bool FINE>
 static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int mlp, bool lds_net, hipStream_t s)
 {
     const dim3 g(nblk);
@@ -1023,34 +1014,33 @@ static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int 
         const size_t net = sizeof(float) * (size_t)a.S * a.H * (DP + 2);
         const size_t mf = sizeof(float) * (size_t)mf_lds_floats<D>() * wpb;
         if (mlp == NEP_MLP_BF16_MFMA)   // BF16 weights (the student)
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetBf16, TRI>), g, blk, mf, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetBf16, FINE>), g, blk, mf, s, a, prm);
         else if (mlp == NEP_MLP_FP32_MFMA)   // FP32 weights as three BF16 terms
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetMf32, TRI>), g, blk, mf, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetMf32, FINE>), g, blk, mf, s, a, prm);
         else if (lds_net && net <= kNetLdsMax)   // network weights staged in LDS
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetLds, TRI>), g, blk, net, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetLds, FINE>), g, blk, net, s, a, prm);
         else
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetGlobal, TRI>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetGlobal, FINE>), g, blk, 0, s, a, prm);
     }
     {
         ProfScope ps_(K_FORCE_ANG, s);
         if (adj_parked(mlp == NEP_MLP_BF16_MFMA || mlp == NEP_MLP_FP32_MFMA, NA1))
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, TRI>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE>), g, blk, 0, s, a, prm);
         else
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, TRI>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE>), g, blk, 0, s, a, prm);
     }
     {
         ProfScope ps_(K_FORCE, s);
-        hipLaunchKernelGGL((k_force_rad<9, TRI>), g, blk, 0, s, a);
+        hipLaunchKernelGGL((k_force_rad<9, FINE>), g, blk, 0, s, a);
     }
 }
 
-// General (triclinic) cells get the kernels with the general pair vector;
-// orthorhombic-only lists the ones without it.
+// Lists with fixed-point positions and lists with fine-grid positions (general cells, long edges).
 template <int NR1, int NA1, bool FOUR>
-static void launch(const NepArgs &a, const float *prm, int nblk, int wpb, bool tri, int mlp, bool lds_net,
+static void launch(const NepArgs &a, const float *prm, int nblk, int wpb, bool fine, int mlp, bool lds_net,
                    hipStream_t s)
 {
-    if (tri) launch_t<NR1, NA1, FOUR, true>(a, prm, nblk, wpb, mlp, lds_net, s);
+    if (fine) launch_t<NR1, NA1, FOUR, true>(a, prm, nblk, wpb, mlp, lds_net, s);
     else launch_t<NR1, NA1, FOUR, false>(a, prm, nblk, wpb, mlp, lds_net, s);
 }
 
@@ -1111,13 +1101,13 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     a.w0b = m->w0b;
     const int mlp = m->mlp;
     const int key = h.n_max_radial * 100 + h.n_max_angular * 10 + h.four_body;
-    const bool tri = nl->any_tri != 0;
+    const bool fine = nl->fine_pos != 0;
     switch (key) {
-    case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, tri, mlp, !ws->net_global, s); break;
-    case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, tri, mlp, !ws->net_global, s); break;
-    case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, tri, mlp, !ws->net_global, s); break;
-    case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, tri, mlp, !ws->net_global, s); break;
-    case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, tri, mlp, !ws->net_global, s); break;
+    case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+    case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+    case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+    case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+    case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
     default: return fail(NEP_ERR_UNSUPPORTED, "nep_compute: unsupported model shape");
     }
     PendingReduce r;

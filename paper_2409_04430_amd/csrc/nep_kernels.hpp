@@ -46,9 +46,10 @@ struct NepArgs {
 struct LaneMap {
     int i, b;        // atom and bead (clamped into range for idle lanes)
     bool valid;      // a real (atom, bead)
+    float fx[6];     // fixed-point quantum (high and low terms)
     int M[3];
     float h[3];
-    int tri;         // general cell: pair vectors through the step vectors hv
+    int form;        // PosForm of the tile's system
     float hv[9];
 };
 __device__ __forceinline__ LaneMap lane_map(const NepArgs &a)
@@ -64,10 +65,12 @@ __device__ __forceinline__ LaneMap lane_map(const NepArgs &a)
     const SysGeom &g = a.geom[a.tile_sys[blockIdx.x]];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
+        m.fx[d] = g.fx[d];
+        m.fx[3 + d] = g.fx[3 + d];
         m.M[d] = g.M[d];
         m.h[d] = g.h[d];
     }
-    m.tri = g.tri;
+    m.form = g.form;
 #pragma unroll
     for (int k = 0; k < 9; ++k) m.hv[k] = g.hv[k];
     return m;
@@ -80,15 +83,15 @@ __device__ __forceinline__ void block_range(const int32_t *uend, int i, int t, i
     s1 = uend[(size_t)i * kMaxSpecies + t];
 }
 
-// Pair vector r_j - r_i from packed positions (see FineGrid).
-// TRI: the launch covers general (triclinic) cells, each lane's system
-// choosing its form (a uniform branch); orthorhombic-only launches take
-// TRI = false and carry no general-cell code.
-template <bool TRI>
+// Pair vector r_j - r_i from packed positions.  FINE = false: every system
+// of the launch has fixed-point positions; otherwise each tile takes its
+// system's form (a uniform branch).
+template <bool FINE>
 __device__ __forceinline__ void pair_vec(const float4 &pj, const float4 &pi, const LaneMap &lm, float &dx, float &dy,
                                          float &dz)
 {
-    if (TRI && lm.tri) packed_pair_tri(pj, pi, lm.M, lm.hv, dx, dy, dz);
+    if (!FINE || lm.form == kPosFixed) fixed_pair(pj, pi, lm.fx, dx, dy, dz);
+    else if (lm.form == kPosGridTri) packed_pair_tri(pj, pi, lm.M, lm.hv, dx, dy, dz);
     else packed_pair(pj, pi, lm.M, lm.h, dx, dy, dz);
 }
 
@@ -161,6 +164,26 @@ __device__ __forceinline__ float4 adj_load(__amdgpu_buffer_rsrc_t r, int q)
 
 constexpr int kBatch = 4;    // neighbours whose index and position are loaded together
 constexpr int kBatchR = 8;   // the same for the descriptor's radial loop
+
+// Index and mask loads of a batch: NB consecutive list entries as 16-byte
+// loads (a row position is only element-aligned, which global memory loads
+// accept).  A batch may reach up to NB - 1 entries past its block: those
+// are entries of the next block, left from an earlier build or the zeros
+// the arrays are created with, so every index read is a valid one and only
+// the contribution is masked off (the arrays end in slack entries).  One
+// address addition and NB / 4 (indices) + NB / 2 (masks) loads per batch
+// instead of a clamp, two additions and two loads per entry.
+template <int NB> struct __attribute__((packed, aligned(4))) idx_run { int32_t v[NB]; };
+template <int NB> struct __attribute__((packed, aligned(8))) mask_run { uint64_t v[NB]; };
+
+// Entry j of an array of rows `stride` bytes long: base + j * stride as one
+// 32 x 32 + 64 bit multiply-add (a size_t product of three factors costs
+// several quarter-rate multiplies per gather).
+template <typename T>
+__device__ __forceinline__ const T *row_at(const T *base, uint32_t j, uint32_t stride)
+{
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (uint64_t)j * stride);
+}
 
 // Hide a uniform pointer from loop-invariant code motion, so that the model
 // coefficients it addresses are re-read through the scalar cache inside a

@@ -25,6 +25,8 @@
 // -> order each cell -> candidate rows (a workgroup per cell, stencil
 // centroids staged in LDS) -> sort rows -> reverse slots; always: union
 // lists.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace nep {
@@ -97,8 +99,8 @@ __device__ void grid_decision(const SysGeom *__restrict__ geom, int nsys, double
                               const float *__restrict__ cmax, int nblk);
 
 // kCenLanes lanes per atom (adjacent), each summing every kCenLanes-th bead
-// (kept in registers for the spread) and packing those beads' positions on
-// the fine grid (the packed positions [N][P] of the list); the atom's sums
+// (kept in registers for the spread) and packing those beads' positions
+// (the packed positions [N][P] of the list); the atom's sums
 // and the bead spread meet by shuffles, and the atom's first lane writes
 // its centroid and spread.  Each workgroup writes its two maxima to
 // cmax[2 blockIdx.x ..] (one store each: same-address atomics from every
@@ -659,8 +661,10 @@ __global__ __launch_bounds__(256) void k_candidates(const double *__restrict__ c
 constexpr double kShellEps = 1e-3;   // A; far above the rounding of d and s
 constexpr int kUnionRounds = 4;      // shell rounds whose partner loads are in flight together
 
-template <bool TRI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TRI ? 4 : 5))) void k_union(const double *__restrict__ pos, const float4 *__restrict__ pos4,
+// FINE: fine-grid positions, general cells possible; otherwise fixed-point
+// positions of orthorhombic cells, with no general-cell code.
+template <bool FINE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 5))) void k_union(const double *__restrict__ pos, const float4 *__restrict__ pos4,
                                                const double *__restrict__ cen, const float *__restrict__ spr, int P,
                                                int N, int S, int lg, const int32_t *__restrict__ atom_sys,
                                                const SysGeom *__restrict__ geom, CutTest cR, CutTest cA,
@@ -728,7 +732,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TRI ? 4 : 5
     const float4 pi = pos4[(size_t)i * P + bb];
     const double *pb = pos + (size_t)bb * N * 3;
     const SysGeom &g = geom[atom_sys[i]];
-    const bool tri = TRI && g.tri;   // orthorhombic-only launches carry no general-cell code
+    const bool tri = FINE && g.tri;
     const uint64_t gmask = (G == 64) ? ~0ull : ((1ull << G) - 1ull);
     const uint64_t full = (P == 64) ? ~0ull : ((1ull << P) - 1ull);
     const double ci0 = cen[3 * (size_t)i], ci1 = cen[3 * (size_t)i + 1], ci2 = cen[3 * (size_t)i + 2];
@@ -789,9 +793,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TRI ? 4 : 5
                 for (int u = 0; u < kUnionRounds; ++u) pj[u] = pos4[(size_t)jq[u] * P + bb];
 #pragma unroll
                 for (int u = 0; u < kUnionRounds; ++u) {
-                    float ex, ey, ez;
-                    packed_pair_g(pj[u], pi, g, tri, ex, ey, ez);
-                    const float r2f = ex * ex + ey * ey + ez * ez;
+                    const float r2f = packed_r2<FINE>(pj[u], pi, g);
                     const bool in = cg < nq[u] && bead_ok && pair_within(r2f, c, pb, i, jq[u], g, tri);
                     const uint64_t m = __ballot(in);
                     uint64_t tk = take[u];
@@ -857,9 +859,7 @@ __global__ __launch_bounds__(256) void k_materialize(const double *__restrict__ 
         int cnt = 0;
         for (int k = 0; k < n; ++k) {
             const int j = row[k] >> 2;
-            float dx, dy, dz;
-            packed_pair_g(pos4[(size_t)j * P + b], pi, g, g.tri, dx, dy, dz);
-            if (pair_within(dx * dx + dy * dy + dz * dz, c, pb, i, j, g, g.tri)) {
+            if (pair_within(packed_r2<true>(pos4[(size_t)j * P + b], pi, g), c, pb, i, j, g, g.tri)) {
                 if (cnt < out) nb[(size_t)cnt * N] = j;
                 ++cnt;
             }
@@ -910,6 +910,8 @@ int32_t update_geometry(const nep_model *m, nep_nlist *nl, const double *boxes, 
             g.hd[a] = fg.hd[a];
             g.Minv[a] = fg.Minv[a];
             g.h[a] = fg.h[a];
+            g.fx[a] = (float)(g.L[a] / 4294967296.0);
+            g.fx[3 + a] = (float)(g.L[a] / 4294967296.0 - (double)g.fx[a]);
             g.M[a] = fg.M[a];
             const int nc = (int)std::floor(ci.w[a] / (rc * (1.0 + 1e-9)));
             g.nc_cap[a] = nc < 1 ? 1 : (nc > 64 ? 64 : nc);
@@ -922,6 +924,8 @@ int32_t update_geometry(const nep_model *m, nep_nlist *nl, const double *boxes, 
                 g.hvd[3 * r + c] = ci.H[3 * r + c] / g.M[r];
                 g.hv[3 * r + c] = (float)g.hvd[3 * r + c];
             }
+        g.form = ci.tri ? kPosGridTri
+                 : std::max({g.L[0], g.L[1], g.L[2]}) > kFixedMaxEdge ? kPosGrid : kPosFixed;
         if (ci.tri) hmax = std::max(hmax, fg.hd[0] + fg.hd[1] + fg.hd[2]);   // offsets span the skewed fine cell
         if (diff) {
             changed = true;
@@ -938,7 +942,11 @@ int32_t update_geometry(const nep_model *m, nep_nlist *nl, const double *boxes, 
     margin = (float)(1e-3 * std::max(1.0, hmax * hmax) * std::max(1.0, rc * rc / 36.0));
     nl->margin = margin;
     nl->any_tri = 0;
-    for (int s = 0; s < nl->nsys; ++s) nl->any_tri |= G[s].tri;
+    nl->fine_pos = 0;
+    for (int s = 0; s < nl->nsys; ++s) {
+        nl->any_tri |= G[s].tri;
+        nl->fine_pos |= G[s].form != kPosFixed;
+    }
     if (!changed) return NEP_OK;
     if (cell_total > nl->ncell_alloc) {
         for (int32_t **p : {&nl->cell_cnt, &nl->cell_start, &nl->cell_sys}) {
@@ -1011,7 +1019,7 @@ extern "C" int32_t neighbor_build_batched(const nep_model *m, nep_nlist *nl, con
         const double rR2 = m->hp.rc_radial * m->hp.rc_radial, rA2 = m->hp.rc_angular * m->hp.rc_angular;
         const CutTest cR{(float)rR2, margin, rR2};
         const CutTest cA{(float)rA2, margin, rA2};
-        auto kern = nl->any_tri ? k_union<true> : k_union<false>;
+        auto kern = nl->fine_pos ? k_union<true> : k_union<false>;
         hipLaunchKernelGGL(kern, dim3(div_up(N, kBlock / 64), 2), dim3(kBlock), 0, s, pos,
                            reinterpret_cast<const float4 *>(nl->pos4), nl->cen, nl->spr, P, N, nl->S, lg, nl->atom_sys, nl->geom, cR,
                            cA, nl->candR, nl->offR, nl->candA, nl->offA, nl->candRs, nl->candAs, nl->lenR, nl->lenA,

@@ -114,7 +114,7 @@ __global__ void k_residual(const float *__restrict__ F, const float *__restrict_
 // second pass over the angular neighbours (one n at a time) accumulates
 // f_k (X.Y + B.Ydot) + fdot_k (u.d) (B.Y) into the row.
 constexpr int kJvpGroup = 2;   // angular radial functions accumulated per neighbour pass
-template <int NR1, int NA1, int KR1, int KA1>
+template <int NR1, int NA1, int KR1, int KA1, bool FINE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_train_jvp(NepArgs a, TrainArgs ta, const float *__restrict__ prm)
 {
@@ -177,7 +177,7 @@ void k_train_jvp(NepArgs a, TrainArgs ta, const float *__restrict__ prm)
                 if (!((mR[s] >> b) & 1u)) continue;
                 const int j = uR[s];
                 float dx, dy, dz;
-                pair_vec<true>(p4[(size_t)j * P + b], pi, lm, dx, dy, dz);
+                pair_vec<FINE>(p4[(size_t)j * P + b], pi, lm, dx, dy, dz);
                 const float r2 = dx * dx + dy * dy + dz * dz;
                 const float rinv = __builtin_amdgcn_rsqf(r2);
                 const float r = r2 * rinv;
@@ -240,7 +240,7 @@ void k_train_jvp(NepArgs a, TrainArgs ta, const float *__restrict__ prm)
                     if (!((mA[s] >> b) & 1u)) continue;
                     const int j = rowA[uA[s]] >> 2;
                     float dx, dy, dz;
-                    pair_vec<true>(p4[(size_t)j * P + b], pi, lm, dx, dy, dz);
+                    pair_vec<FINE>(p4[(size_t)j * P + b], pi, lm, dx, dy, dz);
                     const float r2 = dx * dx + dy * dy + dz * dz;
                     const float rinv = __builtin_amdgcn_rsqf(r2);
                     const float r = r2 * rinv;
@@ -372,7 +372,7 @@ void k_train_jvp(NepArgs a, TrainArgs ta, const float *__restrict__ prm)
                     if (!((mA[s] >> b) & 1u)) continue;
                     const int j = rowA[uA[s]] >> 2;
                     float dx, dy, dz;
-                    pair_vec<true>(p4[(size_t)j * P + b], pi, lm, dx, dy, dz);
+                    pair_vec<FINE>(p4[(size_t)j * P + b], pi, lm, dx, dy, dz);
                     const float r2 = dx * dx + dy * dy + dz * dz;
                     const float rinv = __builtin_amdgcn_rsqf(r2);
                     const float r = r2 * rinv;
@@ -520,9 +520,11 @@ __global__ void k_adam(float *__restrict__ th, const float *__restrict__ g, floa
 }
 
 template <int NR1, int NA1>
-static void launch_jvp(const NepArgs &a, const TrainArgs &t, const float *prm, int nblk, int wpb, hipStream_t s)
+static void launch_jvp(const NepArgs &a, const TrainArgs &t, const float *prm, int nblk, int wpb, bool fine,
+                       hipStream_t s)
 {
-    hipLaunchKernelGGL((k_train_jvp<NR1, NA1, 9, 9>), dim3(nblk), dim3(64 * wpb), 0, s, a, t, prm);
+    if (fine) hipLaunchKernelGGL((k_train_jvp<NR1, NA1, 9, 9, true>), dim3(nblk), dim3(64 * wpb), 0, s, a, t, prm);
+    else hipLaunchKernelGGL((k_train_jvp<NR1, NA1, 9, 9, false>), dim3(nblk), dim3(64 * wpb), 0, s, a, t, prm);
 }
 
 }  // namespace nep
@@ -657,9 +659,9 @@ extern "C" int32_t nep_param_grad_batched(const nep_model *m, nep_nlist *nl, nep
     fill_u32(reinterpret_cast<uint32_t *>(tw->rows), 0xffffffffu, PN * tw->RW, s);
     const int key = h.n_max_radial * 100 + h.n_max_angular * 10;
     switch (key) {
-    case 440: launch_jvp<5, 5>(a, t, m->dev, ws->nblk, ws->wpb, s); break;
-    case 640: launch_jvp<7, 5>(a, t, m->dev, ws->nblk, ws->wpb, s); break;
-    case 860: launch_jvp<9, 7>(a, t, m->dev, ws->nblk, ws->wpb, s); break;
+    case 440: launch_jvp<5, 5>(a, t, m->dev, ws->nblk, ws->wpb, nl->fine_pos != 0, s); break;
+    case 640: launch_jvp<7, 5>(a, t, m->dev, ws->nblk, ws->wpb, nl->fine_pos != 0, s); break;
+    case 860: launch_jvp<9, 7>(a, t, m->dev, ws->nblk, ws->wpb, nl->fine_pos != 0, s); break;
     default: return fail(NEP_ERR_UNSUPPORTED, "nep_param_grad: unsupported model shape");
     }
     const int S = h.n_species, H = h.hidden, D = h.dim, NR1 = h.n_max_radial + 1, KR1 = h.basis_radial + 1;
