@@ -8,6 +8,7 @@
 #include <sstream>
 
 #include "internal.hpp"
+#include "nep_small.hpp"
 
 namespace nep {
 
@@ -657,20 +658,26 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
     if (e == hipSuccess) e = dalloc(&nl->candAs, Nn * capA);
     if (e == hipSuccess) e = dalloc(&nl->lenR, Nn);
     if (e == hipSuccess) e = dalloc(&nl->offR, Nn * (kMaxSpecies + 1));
-    if (e == hipSuccess) e = dalloc(&nl->candA, Nn * capA);
     if (e == hipSuccess) e = dalloc(&nl->lenA, Nn);
     if (e == hipSuccess) e = dalloc(&nl->offA, Nn * (kMaxSpecies + 1));
-    if (e == hipSuccess) e = dalloc(&nl->revA, Nn * capA);
     // The force kernels read list entries in batches that may run past a
     // block, into other valid entries: the arrays start out as zeros (every
     // entry a valid index) and end in slack, a batch past the last row and,
     // in the angular force, the longest block of a wavefront more.
-    const size_t slack = (size_t)capA + 16;
-    if (e == hipSuccess) e = dalloc(&nl->uniR, Nn * capR + slack);
-    if (e == hipSuccess) e = dalloc(&nl->umR, Nn * capR + slack);
-    if (e == hipSuccess) e = dalloc(&nl->umA, Nn * capA + slack);
+    // One allocation and one fill for all of them.
+    const size_t slack = (size_t)capA + 16, nR = Nn * capR + slack, nA = Nn * capA + slack;
+    const size_t words = 3 * nR + 3 * nA + 2 * Nn * capA;   // 64-bit masks first
+    if (e == hipSuccess) e = dalloc(&nl->lists, words);
+    if (e == hipSuccess) e = hipMemset(nl->lists, 0, sizeof(int32_t) * words);
+    if (e == hipSuccess) {
+        nl->umR = reinterpret_cast<uint64_t *>(nl->lists);
+        nl->umA = nl->umR + nR;
+        nl->uniR = reinterpret_cast<int32_t *>(nl->umA + nA);
+        nl->uniA = nl->uniR + nR;
+        nl->candA = nl->uniA + nA;
+        nl->revA = nl->candA + Nn * capA;
+    }
     if (e == hipSuccess) e = dalloc(&nl->uendR, Nn * kMaxSpecies);
-    if (e == hipSuccess) e = dalloc(&nl->uniA, Nn * capA + slack);
     if (e == hipSuccess) e = dalloc(&nl->uendA, Nn * kMaxSpecies);
     if (e == hipSuccess) e = dalloc(&nl->pairbuf, 4 * PN * capA);
     if (e == hipSuccess) e = dalloc(&nl->pos4, 4 * PN);
@@ -678,12 +685,6 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
     if (e == hipSuccess) e = dalloc(&nl->grid, 16 + kDevSysWords * (size_t)nsys);
     if (e == hipSuccess) e = dalloc(&nl->status, 8);
     if (e == hipSuccess) e = hipMemset(nl->status, 0, 8 * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMemset(nl->uniR, 0, sizeof(int32_t) * (Nn * capR + slack));
-    if (e == hipSuccess) e = hipMemset(nl->uniA, 0, sizeof(int32_t) * (Nn * capA + slack));
-    if (e == hipSuccess) e = hipMemset(nl->umR, 0, sizeof(uint64_t) * (Nn * capR + slack));
-    if (e == hipSuccess) e = hipMemset(nl->umA, 0, sizeof(uint64_t) * (Nn * capA + slack));
-    if (e == hipSuccess && Nn) e = hipMemset(nl->candA, 0, sizeof(int32_t) * Nn * capA);
-    if (e == hipSuccess && Nn) e = hipMemset(nl->revA, 0, sizeof(int32_t) * Nn * capA);
     // pair terms start at zero: a slot that a step with truncated rows leaves
     // unwritten then holds a finite stale value, never uninitialised bits
     if (e == hipSuccess && PN) e = hipMemset(nl->pairbuf, 0, sizeof(float) * 4 * PN * capA);
@@ -714,8 +715,7 @@ extern "C" void nep_nlist_destroy(nep_nlist *nl)
 {
     if (!nl) return;
     for (void *p : {(void *)nl->geom, (void *)nl->atom_sys, (void *)nl->cell_sys, (void *)nl->cen, (void *)nl->spr, (void *)nl->cmax, (void *)nl->cen_ref, (void *)nl->candR, (void *)nl->candRs, (void *)nl->candAs, (void *)nl->lenR, (void *)nl->offR,
-                    (void *)nl->candA, (void *)nl->lenA, (void *)nl->offA, (void *)nl->revA, (void *)nl->uniR,
-                    (void *)nl->umR, (void *)nl->umA, (void *)nl->uendR, (void *)nl->uniA, (void *)nl->uendA, (void *)nl->pairbuf, (void *)nl->pos4, (void *)nl->posT,
+                    (void *)nl->lists, (void *)nl->lenA, (void *)nl->offA, (void *)nl->uendR, (void *)nl->uendA, (void *)nl->pairbuf, (void *)nl->pos4, (void *)nl->posT,
                     (void *)nl->cell_cnt, (void *)nl->cell_start, (void *)nl->cell_atoms, (void *)nl->grid,
                     (void *)nl->status})
         if (p) (void)hipFree(p);
@@ -865,6 +865,7 @@ extern "C" int32_t nep_ws_create_batched(const nep_model *m, int32_t P, int32_t 
     if (e == hipSuccess) e = dalloc(&w->partE, (size_t)std::max(P, 1) * nb);
     if (e == hipSuccess) e = dalloc(&w->partW, (size_t)2 * std::max(P, 1) * nb * 9);
     if (e == hipSuccess) e = dalloc(&w->Fang, PN * 3);
+    if (P > 0 && N > 0 && (int64_t)PN <= kSmallRows && e == hipSuccess) e = dalloc(&w->rowp, (size_t)kRowValues * PN);
     if (e == hipSuccess) e = dalloc(&w->flags, 4);
     if (e == hipSuccess) e = hipMemset(w->flags, 0, 4 * sizeof(uint32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -887,7 +888,7 @@ extern "C" int32_t nep_ws_create(const nep_model *m, int32_t P, int32_t N, nep_w
 extern "C" void nep_ws_destroy(nep_ws *w)
 {
     if (!w) return;
-    for (void *p : {(void *)w->B, (void *)w->Gad, (void *)w->arad, (void *)w->partE, (void *)w->partW, (void *)w->Fang,
+    for (void *p : {(void *)w->rowp, (void *)w->B, (void *)w->Gad, (void *)w->arad, (void *)w->partE, (void *)w->partW, (void *)w->Fang,
                     (void *)w->flags, (void *)w->tile_atom0, (void *)w->tile_atom1, (void *)w->tile_sys,
                     (void *)w->sys_tile0})
         if (p) (void)hipFree(p);

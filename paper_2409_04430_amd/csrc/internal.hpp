@@ -142,6 +142,7 @@ struct nep_nlist {
     float *spr = nullptr;         // [N] largest bead distance from the centroid (rounded up) of this call
     float *cmax = nullptr;        // [ceil(kCenLanes N / kBlock)][2] per-workgroup maxima of the centroid kernel
     double *cen_ref = nullptr;    // [N][3] centroids at the last rebuild
+    int32_t *lists = nullptr;     // one allocation: umR, umA, uniR, uniA, candA, revA
     int32_t *candR = nullptr;     // [N][capR] entries (j << 2) | species(j), sorted by (species, j)
     int32_t *candRs = nullptr;    // [N][capR] the same rows unsorted, as the candidate search leaves them
     int32_t *candAs = nullptr;    // [N][capA] the angular rows unsorted
@@ -181,6 +182,12 @@ struct PendingReduce {
     const int32_t *sys_tile0 = nullptr;
     int P = 0, nblk = 0;
     int nout = 0;              // outputs: systems x P x 10 (energy, 9 virial entries); 0 = nothing pending
+    // small systems: per-(bead, atom) values [19][P][N] (site energy, 9 angular
+    // and 9 radial virial entries) in place of the partials, each tile's sum
+    // taken here over the same atoms in the same order
+    const float *rowp = nullptr;
+    const int32_t *tile_atom0 = nullptr, *tile_atom1 = nullptr;
+    int N = 0;
     double *E = nullptr, *W = nullptr;
 };
 
@@ -207,6 +214,7 @@ struct nep_ws {
     double *partW = nullptr;   // angular pass [P][9][nblk], then radial pass [P][9][nblk] (room for nblk_cap)
     float *Fang = nullptr;     // [N][P][3] angular part of the forces
     uint32_t *flags = nullptr; // [1]
+    float *rowp = nullptr;     // small systems (nep_small.hip): per-(bead, atom) energy and virial values [19][P][N]
     int defer_next = 0;        // the next nep_compute leaves its E/W sums pending (nep_ws_defer_reduce)
     PendingReduce pending;     // sums of a deferred call, until an integrator launch completes them
 };
@@ -259,6 +267,18 @@ __device__ __forceinline__ void reduce_output(const PendingReduce &r, int o, int
     const double *pr = c == 0 ? nullptr : r.partWr + ((size_t)b * 9 + (c - 1)) * r.nblk;
     double acc = 0.0;
     int k = k0 + t;
+    if (r.rowp) {
+        const size_t PN = (size_t)r.P * r.N;
+        const float *va = r.rowp + (size_t)c * PN + (size_t)b * r.N, *vr = va + 9 * PN;
+        for (; k < k1; k += 64) {
+            const int a0 = r.tile_atom0[k], a1 = r.tile_atom1[k];
+            double sa = 0.0, sr = 0.0;
+            for (int i = a0; i < a1; ++i) sa += (double)va[i];
+            if (c)
+                for (int i = a0; i < a1; ++i) sr += (double)vr[i];
+            acc += sa + sr;
+        }
+    }
     for (; k + 192 < k1; k += 256) {
         double v[4];
 #pragma unroll
@@ -329,6 +349,7 @@ __device__ __forceinline__ float4 pack_fixed(const double *x3, const SysGeom &g)
 __device__ __forceinline__ void fixed_pair(const float4 &pj, const float4 &pi, const float fx[6], float &dx, float &dy,
                                            float &dz)
 {
+#pragma clang fp contract(off)
     const float cx = (float)(int32_t)(__float_as_uint(pj.x) - __float_as_uint(pi.x));
     const float cy = (float)(int32_t)(__float_as_uint(pj.y) - __float_as_uint(pi.y));
     const float cz = (float)(int32_t)(__float_as_uint(pj.z) - __float_as_uint(pi.z));

@@ -23,223 +23,10 @@
 // loads, SGPR operands).  Neighbour loops keep several gathers in flight.
 #include "internal.hpp"
 #include "nep_kernels.hpp"
+#include "nep_net.hpp"
+#include "nep_small.hpp"
 
 namespace nep {
-
-// ------------------------------------------ matrix-core network ---
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Orders this wavefront's LDS writes before its later LDS reads (LDS
-// operations of one wavefront complete in issue order).
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Eight FP32 values as three BF16 vectors whose sum is exact: truncation
-// keeps the top 8 significant bits, the remainder's top 8 bits follow, and
-// the last remainder has at most 8 significant bits left.
-__device__ __forceinline__ void split3(const float (&x)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const uint32_t u0 = __float_as_uint(x[e]) & 0xffff0000u;
-        const float r1 = x[e] - __uint_as_float(u0);
-        const uint32_t u1 = __float_as_uint(r1) & 0xffff0000u;
-        const float r2 = r1 - __uint_as_float(u1);
-        hi[e] = __builtin_bit_cast(__bf16, (uint16_t)(u0 >> 16));
-        mid[e] = __builtin_bit_cast(__bf16, (uint16_t)(u1 >> 16));
-        lo[e] = __builtin_bit_cast(__bf16, (uint16_t)(__float_as_uint(r2) >> 16));
-    }
-}
-
-// C += A B over the BF16 terms of both operands: A (weights) with WT terms,
-// B (activations) with three.  WT = 1: the three products; WT = 3: the six
-// products of term indices i + j <= 2 (a dropped product is below 2^-22 of
-// the full one).
-template <int WT>
-__device__ __forceinline__ f32x4 mfma_terms(const bf16x8 (&a)[WT], const bf16x8 (&b)[3], f32x4 c)
-{
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], c, 0, 0, 0);
-    if constexpr (WT == 3) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], c, 0, 0, 0);
-    }
-    return c;
-}
-
-// tanh and its slope, both to a few units in the last place over the whole
-// range.  With a = |z| and r = 2 / (exp(2 a) + 1) in (0, 1]:
-// |tanh z| = 1 - r and 1 - tanh^2 z = r (2 - r), free of cancellation for
-// a >= 1/2 (r <= 0.54) and, for the slope, everywhere (exp saturates to inf
-// for large a, so r = 0).  Below a = 1/2, tanh z = z f(z^2) with f the
-// Maclaurin series of tanh(z) / z, whose coefficients are
-// 2^2k (2^2k - 1) B_2k / (2k)! (B the Bernoulli numbers); through z^15 the
-// series is exact to 1e-8 relative there.
-__device__ __forceinline__ void tanh_and_slope(float z, float &h, float &dh)
-{
-    const float a = fabsf(z);
-    const float r = 2.0f * __builtin_amdgcn_rcpf(__expf(2.0f * a) + 1.0f);
-    dh = r * (2.0f - r);
-    const float t = z * z;
-    float f = -929569.0f / 638512875.0f;
-    f = fmaf(f, t, 21844.0f / 6081075.0f);
-    f = fmaf(f, t, -1382.0f / 155925.0f);
-    f = fmaf(f, t, 62.0f / 2835.0f);
-    f = fmaf(f, t, -17.0f / 315.0f);
-    f = fmaf(f, t, 2.0f / 15.0f);
-    f = fmaf(f, t, -1.0f / 3.0f);
-    f = fmaf(f, t, 1.0f);
-    h = a < 0.5f ? z * f : copysignf(1.0f - r, z);
-}
-
-// The network of the wavefront's 64 (atom, bead) rows on the matrix cores,
-// as transposed products: Z^T = W0 Qh^T (A operand = weights, rows = hidden
-// units; B operand = the scaled descriptors, columns = rows of the batch),
-// h = tanh(Z - b0), U = w1 . h - b1, and G^T = W0^T (w1 (1 - h^2))^T.  The
-// hidden units of a forward result tile sit in the lanes exactly where the
-// adjoint product takes them as its B operand (its K order is permuted to
-// match, in the weight fragments), so the hidden layer never leaves
-// registers.  Qh is staged once in this wavefront's LDS tile X (64 rows of
-// XS floats); each row's G and U are written back over it.  Zero rows for
-// lanes outside the current species (mine = false).  Returns U of the
-// lane's row and G (without the descriptor scale) in G[0..D).
-template <int D, int WT>
-__device__ float mlp_mf(const float (&qh)[D], bool mine, const uint16_t *__restrict__ frag, const float *b0,
-                        const float *w1, float b1, int H, float *X, float (&G)[D])
-{
-    constexpr int DP = D <= 32 ? 32 : 64, KC = DP / 32, DT = DP / 16, XS = DP + 4;
-    // batch tiles (16 rows each) per pass: every weight fragment is loaded
-    // once per pass, and a pass keeps its tiles' operands and accumulators
-    // in registers
-    constexpr int JB = DP == 32 ? 4 : 2;
-    const int HC = (H + 31) >> 5, HT = 2 * HC;
-    const int l = threadIdx.x & 63, c = l & 15, g = l >> 4;
-#pragma unroll
-    for (int v4 = 0; v4 < DP / 4; ++v4) {
-        float w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int v = 4 * v4 + e;
-            w[e] = (mine && v < D) ? qh[v < D ? v : 0] : 0.0f;
-        }
-        *reinterpret_cast<float4 *>(X + l * XS + 4 * v4) = make_float4(w[0], w[1], w[2], w[3]);
-    }
-    wave_lds_sync();
-    const bf16x8 *fw = reinterpret_cast<const bf16x8 *>(frag) + l;   // one 8-entry fragment per lane and block
-    const int fwd = HT * KC, tstride = fwd + DT * HC;                 // blocks per term
-    for (int j0 = 0; j0 < 4; j0 += JB) {
-        // B operands of the forward product: column c of tile j = batch row 16 j + c
-        bf16x8 xb[JB][KC][3];
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            const float *xr = X + (16 * (j0 + jj) + c) * XS + 8 * g;
-#pragma unroll
-            for (int kc = 0; kc < KC; ++kc) {
-                const float4 a0 = *reinterpret_cast<const float4 *>(xr + 32 * kc);
-                const float4 a1 = *reinterpret_cast<const float4 *>(xr + 32 * kc + 4);
-                const float x8[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                split3(x8, xb[jj][kc][0], xb[jj][kc][1], xb[jj][kc][2]);
-            }
-        }
-        f32x4 gacc[JB][DT];
-        float uacc[JB];
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            uacc[jj] = 0.0f;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) gacc[jj][dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        for (int hc = 0; hc < HC; ++hc) {
-            // this lane's eight hidden units of the chunk: 32 hc + 16 h2 + 4 g + e
-            float bq[8], wq[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int mu = 32 * hc + 16 * (q >> 2) + 4 * g + (q & 3);
-                bq[q] = mu < H ? b0[mu] : 0.0f;
-                wq[q] = mu < H ? w1[mu] : 0.0f;
-            }
-            float gz[JB][8];
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                const int ht = 2 * hc + h2;
-                bf16x8 wa[KC][WT];
-#pragma unroll
-                for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-                    for (int t = 0; t < WT; ++t) wa[kc][t] = fw[(t * tstride + ht * KC + kc) * 64];
-#pragma unroll
-                for (int jj = 0; jj < JB; ++jj) {
-                    f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                    for (int kc = 0; kc < KC; ++kc) z = mfma_terms<WT>(wa[kc], xb[jj][kc], z);
-                    // z[e]: hidden unit 16 ht + 4 g + e of batch row 16 (j0 + jj) + c
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float hh, dh;
-                        tanh_and_slope(z[e] - bq[4 * h2 + e], hh, dh);
-                        uacc[jj] = fmaf(wq[4 * h2 + e], hh, uacc[jj]);
-                        gz[jj][4 * h2 + e] = wq[4 * h2 + e] * dh;
-                    }
-                }
-            }
-            // adjoint: B operand gz^T in K order (4 g + e, 16 + 4 g + e) as in the fragments
-            bf16x8 wt[DT][WT];
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int t = 0; t < WT; ++t) wt[dt][t] = fw[(t * tstride + fwd + dt * HC + hc) * 64];
-#pragma unroll
-            for (int jj = 0; jj < JB; ++jj) {
-                bf16x8 gb[3];
-                split3(gz[jj], gb[0], gb[1], gb[2]);
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) gacc[jj][dt] = mfma_terms<WT>(wt[dt], gb, gacc[jj][dt]);
-            }
-        }
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-            // U of column c: the four lane groups hold different hidden units
-            float u = uacc[jj];
-            u += __shfl_xor(u, 16, 64);
-            u += __shfl_xor(u, 32, 64);
-            // G^T (descriptor 16 dt + 4 g + e, column c) back over the row, which
-            // this wavefront has finished reading (its LDS operations run in order)
-            float *xo = X + (16 * (j0 + jj) + c) * XS;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-                *reinterpret_cast<float4 *>(xo + 16 * dt + 4 * g) =
-                    make_float4(gacc[jj][dt][0], gacc[jj][dt][1], gacc[jj][dt][2], gacc[jj][dt][3]);
-            if (g == 0) xo[DP] = u;
-        }
-    }
-    wave_lds_sync();
-#pragma unroll
-    for (int v = 0; v < D; ++v) G[v] = X[l * XS + v];
-    const float u = X[l * XS + DP] - b1;
-    wave_lds_sync();   // X is rewritten by the next species of this wavefront
-    return u;
-}
-
-// LDS floats per wavefront of the matrix-core network.
-template <int D>
-constexpr int mf_lds_floats() { return 64 * ((D <= 32 ? 32 : 64) + 4); }
-
-// Network arithmetic of k_descriptor: FP32 vector units with the weights
-// read from global memory or staged in LDS; BF16 matrix cores with BF16
-// weights (the student); or BF16 matrix cores with the FP32 weights as
-// three exact BF16 terms (FP32 accuracy).  (FP32 operands on the matrix
-// cores, 16 x 16 x 4 FP32 tiles, measured slower than the LDS-staged vector
-// form: two wavefronts per SIMD cannot hide their dependent chains.)
-constexpr int kNetGlobal = 0, kNetLds = 1, kNetBf16 = 2, kNetMf32 = 3;
-constexpr int kNetRowRegs = 40;   // longest descriptor whose weight rows the LDS network holds in registers
 
 // ----------------------------------------------------------- pass 1 ---
 
@@ -330,7 +117,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                     if (in[u]) {
                         float dx, dy, dz;
                         pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
-                        const float r2 = dx * dx + dy * dy + dz * dz;
+                        const float r2 = norm2(dx, dy, dz);
                         {
                             // sk[0] collects f_c, sk[k > 0] collects f_c T_k
                             const float r = __builtin_amdgcn_sqrtf(r2);
@@ -410,7 +197,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                     if (!in[u]) continue;
                     float dx, dy, dz;
                     pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
-                    const float r2 = dx * dx + dy * dy + dz * dz;
+                    const float r2 = norm2(dx, dy, dz);
                     const float rinv = __builtin_amdgcn_rsqf(r2);
                     const float r = r2 * rinv;
                     float fc, T[KA1];
@@ -444,18 +231,11 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                 float s2 = 0.0f;
 #pragma unroll
                 for (int m = 0; m < kNumSH; ++m)
-                    if (sh_l(m) == l) s2 += A[g][m] * A[g][m];
+                    if (sh_l(m) == l) s2 = fmaf(A[g][m], A[g][m], s2);
                 q[NR1 + (l - 1) * NA1 + n] = s2;
             }
             if (FOUR) {
-                float M[5];
-                m_from_l2(&A[g][3], shc, M);
-                const float mxy = M[0], myz = M[1], mzz = M[2], mxz = M[3], dd = M[4];
-                const float mxx = 0.5f * (dd - mzz), myy = 0.5f * (-dd - mzz);
-                const float tr3 = mxx * mxx * mxx + myy * myy * myy + mzz * mzz * mzz +
-                                  3.0f * mxx * (mxy * mxy + mxz * mxz) + 3.0f * myy * (mxy * mxy + myz * myz) +
-                                  3.0f * mzz * (mxz * mxz + myz * myz) + 6.0f * mxy * myz * mxz;
-                q[NR1 + kLmax * NA1 + n] = a.kappa4 * tr3;
+                q[NR1 + kLmax * NA1 + n] = a.kappa4 * four_body_tr3(&A[g][3], shc);
             }
             if constexpr (PARK) {
                 // park A in this lane's adjoint row (the angular force kernel forms B from it)
@@ -760,7 +540,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                     dy = 0.0f;
                     dz = 0.0f;
                 }
-                const float r2 = dx * dx + dy * dy + dz * dz;
+                const float r2 = norm2(dx, dy, dz);
                 const float rinv = __builtin_amdgcn_rsqf(r2);
                 const float r = r2 * rinv;
                 const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
@@ -785,11 +565,9 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                 }
                 float sY, gx, gy, gz;
                 // B^i is stored as B_nlm c_m: bare polynomials here
-                adjoint_contract<NA1>(ux, uy, uz, UnitNorm{}, Bi, gij, gpij, sY, gx, gy, gz);
-                const float ug = ux * gx + uy * gy + uz * gz;
-                const float px = sY * ux + (gx - ux * ug) * rinv;
-                const float py = sY * uy + (gy - uy * ug) * rinv;
-                const float pz = sY * uz + (gz - uz * ug) * rinv;
+                adjoint_contract<NA1>(ux, uy, uz, Bi, gij, gpij, sY, gx, gy, gz);
+                float px, py, pz;
+                pair_term(ux, uy, uz, rinv, sY, gx, gy, gz, px, py, pz);
                 if (act) {
                     const int rk = rq[u];
                     if (rk >= 0)
@@ -894,24 +672,9 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
                     if (in[u]) {
                         float dx, dy, dz;
                         pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
-                        const float r2 = dx * dx + dy * dy + dz * dz;
-                        const float rinv = __builtin_amdgcn_rsqf(r2);
-                        const float r = r2 * rinv;
-                        // sum_k A_k f_k' = (dx/dr f_c sum A_k T_k' + f_c' sum A_k (T_k + 1)) / 2,
-                        // sum_{k>0} A_k (T_k + 1) = sum_{k>0} A_k T_k + (the stored sums of a_k)
-                        float fc, fcp, dxdr, T[KR1], Tp[KR1];
-                        cheb_td<KR1>(r, a.rcRinv, fc, fcp, dxdr, T, Tp);
-                        float s1 = 2.0f * (ai[0] + aj[u][0]) + (ai[KR1] + aj[u][KR1]), s2 = 0.0f;
-#pragma unroll
-                        for (int q2 = 1; q2 < KR1; ++q2) {
-                            const float A = ai[q2] + aj[u][q2];
-                            s1 = fmaf(A, T[q2], s1);
-                            s2 = fmaf(A, Tp[q2], s2);
-                        }
-                        const float sc = 0.5f * fmaf(dxdr * fc, s2, fcp * s1);
-                        const float w = sc * rinv;
+                        const float w = radial_pair_w<KR1>(norm2(dx, dy, dz), a.rcRinv, ai, aj[u]);
                         const float qx = w * dx, qy = w * dy, qz = w * dz;
-                        bx += qx; by += qy; bz += qz;
+                        bx = fmaf(w, dx, bx); by = fmaf(w, dy, by); bz = fmaf(w, dz, bz);
                         const float hx = -0.5f * dx, hy = -0.5f * dy, hz = -0.5f * dz;
                         // a central pair term: r (x) q is symmetric, six entries
                         Wf[0] = fmaf(hx, qx, Wf[0]); Wf[1] = fmaf(hx, qy, Wf[1]); Wf[2] = fmaf(hx, qz, Wf[2]);
@@ -1024,7 +787,10 @@ static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int 
     }
     {
         ProfScope ps_(K_FORCE_ANG, s);
-        if (adj_parked(mlp == NEP_MLP_BF16_MFMA || mlp == NEP_MLP_FP32_MFMA, NA1))
+        const bool parked = adj_parked(mlp == NEP_MLP_BF16_MFMA || mlp == NEP_MLP_FP32_MFMA, NA1);
+        if constexpr (adj_parked(false, NA1))   // wide sets are always parked
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE>), g, blk, 0, s, a, prm);
+        else if (parked)
             hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE>), g, blk, 0, s, a, prm);
         else
             hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE>), g, blk, 0, s, a, prm);
@@ -1100,19 +866,26 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     a.ow1 = m->off.w1; a.ob1 = m->off.b1; a.osh = m->off.sh;
     a.w0b = m->w0b;
     const int mlp = m->mlp;
-    const int key = h.n_max_radial * 100 + h.n_max_angular * 10 + h.four_body;
-    const bool fine = nl->fine_pos != 0;
-    switch (key) {
-    case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-    case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-    case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-    case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-    case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-    default: return fail(NEP_ERR_UNSUPPORTED, "nep_compute: unsupported model shape");
-    }
     PendingReduce r;
-    r.partE = ws->partE; r.partWa = a.partWa; r.partWr = a.partWr; r.sys_tile0 = ws->sys_tile0;
-    r.P = P; r.nblk = ws->nblk; r.nout = nsys * P * 10; r.E = E; r.W = W;
+    r.sys_tile0 = ws->sys_tile0; r.P = P; r.nblk = ws->nblk; r.nout = nsys * P * 10; r.E = E; r.W = W;
+    const bool small = ws->rowp && takes_small((int64_t)P * N, mlp);
+    if (small) {   // one wavefront per (atom, bead)
+        const int32_t rcs = launch_small(a, m, nl->atom_sys, ws->rowp, s);
+        if (rcs != NEP_OK) return rcs;
+        r.rowp = ws->rowp; r.tile_atom0 = ws->tile_atom0; r.tile_atom1 = ws->tile_atom1; r.N = N;
+    } else {
+        const int key = h.n_max_radial * 100 + h.n_max_angular * 10 + h.four_body;
+        const bool fine = nl->fine_pos != 0;
+        switch (key) {
+        case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+        case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+        case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+        case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+        case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+        default: return fail(NEP_ERR_UNSUPPORTED, "nep_compute: unsupported model shape");
+        }
+        r.partE = ws->partE; r.partWa = a.partWa; r.partWr = a.partWr;
+    }
     if (defer) {   // completed by the next integrator launch (trpmd_step_nep)
         ws->pending = r;
     } else {
