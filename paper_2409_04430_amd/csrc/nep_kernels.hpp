@@ -76,6 +76,27 @@ __device__ __forceinline__ LaneMap lane_map(const NepArgs &a)
     return m;
 }
 
+// The same for kernels with one (atom, bead) per wavefront: the geometry of
+// the atom's system, uniform over the wavefront.
+__device__ __forceinline__ LaneMap row_map(const SysGeom &g, int i, int b)
+{
+    LaneMap m;
+    m.i = i;
+    m.b = b;
+    m.valid = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        m.fx[d] = g.fx[d];
+        m.fx[3 + d] = g.fx[3 + d];
+        m.M[d] = g.M[d];
+        m.h[d] = g.h[d];
+    }
+    m.form = g.form;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) m.hv[k] = g.hv[k];
+    return m;
+}
+
 // Start and end of species block t in a union list.
 __device__ __forceinline__ void block_range(const int32_t *uend, int i, int t, int &s0, int &s1)
 {

@@ -30,26 +30,6 @@ namespace nep {
 constexpr int kNetVector = 0;   // FP32 vector units (kNetBf16 and kNetMf32 as in nep.hip)
 constexpr int kYPad = 25;       // row stride of the 24 harmonics in LDS (odd: no bank conflicts across lanes)
 
-// The geometry of the row's system, uniform over the wavefront.
-__device__ __forceinline__ LaneMap row_map(const SysGeom &g, int i, int b)
-{
-    LaneMap m;
-    m.i = i;
-    m.b = b;
-    m.valid = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        m.fx[d] = g.fx[d];
-        m.fx[3 + d] = g.fx[3 + d];
-        m.M[d] = g.M[d];
-        m.h[d] = g.h[d];
-    }
-    m.form = g.form;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) m.hv[k] = g.hv[k];
-    return m;
-}
-
 template <int NR1, int NA1, bool FOUR, int NET>
 __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__restrict__ prm,
                                                    const int32_t *__restrict__ atom_sys, float *__restrict__ rowp)
