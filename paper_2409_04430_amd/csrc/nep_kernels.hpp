@@ -146,8 +146,8 @@ __device__ __forceinline__ void bead_block_sum(double v, double *lds, int P, int
 // the workspace's tile table; the array holds a row for every lane of a
 // launch, idle lanes included (never written; zero from creation).  The
 // accesses go through a buffer resource over the wavefront's rows: the
-// lane's byte offset in a vector register, the float4 index as a scalar
-// offset, so that no per-float4 64-bit address is kept in registers (the
+// lane's byte offset in a vector register, for loads the float4 index as a
+// scalar offset, so that no per-float4 64-bit address is kept in registers (the
 // rows of one lane span more than the immediate offset of a global access).
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kBufWord3 = 0x00020000;   // buffer resource word 3 of gfx9-family chips: 32-bit data format
@@ -171,10 +171,18 @@ constexpr bool adj_parked(bool matrix_core_net, int NA1) { return matrix_core_ne
 // the four-body adjoints four to an entry.
 constexpr int gad_q(int NA1, bool four) { return NA1 + (four ? (NA1 + 3) / 4 : 0); }
 
+// The store's offset stays out of the scalar offset operand: a 16-byte buffer
+// store reads its data registers over several cycles, and the compiler keeps
+// the next instructions from overwriting them only where the scalar offset is
+// a constant.  With the offset there, a vector instruction directly behind
+// the store replaced the last four lanes of each sixteen in about 3 % of the
+// descriptor launches of a 9 + 9 radial function model (32000 atoms x 32).
 __device__ __forceinline__ void adj_store(__amdgpu_buffer_rsrc_t r, int q, float4 v)
 {
     const u32x4_t u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-    __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)(threadIdx.x & 63) * 16, q * 1024, 0);
+    int o = (int)(threadIdx.x & 63) * 16;
+    asm("" : "+v"(o));   // keeps q * 1024 an addition, whose low part becomes the immediate offset
+    __builtin_amdgcn_raw_buffer_store_b128(u, r, o + q * 1024, 0, 0);
 }
 
 __device__ __forceinline__ float4 adj_load(__amdgpu_buffer_rsrc_t r, int q)
