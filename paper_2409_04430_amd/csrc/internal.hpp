@@ -140,6 +140,7 @@ struct nep_nlist {
     // Shared by all beads: ring-polymer centroids and candidate rows.
     double *cen = nullptr;        // [N][3] centroids of this call
     float *spr = nullptr;         // [N] largest bead distance from the centroid (rounded up) of this call
+    float *cen4 = nullptr;        // [N][4] centroid in the fixed-point form and its spread (systems of that form)
     float *cmax = nullptr;        // [ceil(kCenLanes N / kBlock)][2] per-workgroup maxima of the centroid kernel
     double *cen_ref = nullptr;    // [N][3] centroids at the last rebuild
     int32_t *lists = nullptr;     // one allocation: umR, umA, uniR, uniA, candA, revA

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kBlock) void k_centroid(const double *__restrict__ 
                                                      float *__restrict__ spr, const double *__restrict__ cen_ref,
                                                      const SysGeom *__restrict__ geom, const uint32_t *__restrict__ grid,
                                                      uint32_t *__restrict__ status, float4 *__restrict__ pos4,
-                                                     float *__restrict__ cmax)
+                                                     float4 *__restrict__ cen4, float *__restrict__ cmax)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     const int i = t / kCenLanes, q = t % kCenLanes;
@@ -167,7 +167,12 @@ __global__ __launch_bounds__(kBlock) void k_centroid(const double *__restrict__ 
         cen[3 * i + 1] = c[1];
         cen[3 * i + 2] = c[2];
         const bool finite = isfinite(c[0]) && isfinite(c[1]) && isfinite(c[2]) && isfinite(m2);
-        spr[i] = finite ? (float)sqrt(m2) * 1.000001f + 1e-7f : 3.0e38f;
+        const float sp = finite ? (float)sqrt(m2) * 1.000001f + 1e-7f : 3.0e38f;
+        spr[i] = sp;
+        if (g.form == kPosFixed) {   // centroid and spread in one 16-byte record
+            const float4 f4 = pack_fixed(c, g);
+            cen4[i] = make_float4(f4.x, f4.y, f4.z, sp);
+        }
         if (!finite) {
             f |= NEP_FLAG_NONFINITE;
         } else {
@@ -653,19 +658,30 @@ __global__ __launch_bounds__(256) void k_candidates(const double *__restrict__ c
 // the two atoms' largest bead distances from their centroids, every bead
 // pair lies within [d - s, d + s] (the minimum image is the shortest image),
 // so d + s < rc - eps keeps all beads and d - s > rc + eps none (d is the
-// nearest-image distance, also in general cells: mic_vec).  Only the
+// nearest-image distance, also in general cells: mic_vec; in orthorhombic
+// cells d and s come from one 16-byte record per candidate, the centroid in
+// the fixed-point form and the spread: the gathers are bound by the address
+// rate, one cache line per candidate and load).  Only the
 // remaining shell candidates are tested bead by bead (the exact test of the
 // per-bead lists), their G lanes per candidate holding the beads; each mask
 // is written back to its candidate's lane, and the kept candidates are
-// appended with one ballot-ranked store per lane.
+// appended with one ballot-ranked store per lane.  The shell candidates are
+// taken in rank order from one permutation per batch and each lane extracts
+// the mask of its own rank, so a round costs the same at every bead count
+// (found one after another by their bit positions, with a store of each mask,
+// they took 64 / G serial steps a round).  Per call: 16 water boxes of 192 to
+// 3072 atoms x 32 beads 194 -> 95 us, 4608 water atoms 39 -> 27 us, 4096
+// atoms x 32 beads 20.5 -> 12.6 us, 32000 x 32 116 -> 63 us.
 constexpr double kShellEps = 1e-3;   // A; far above the rounding of d and s
+constexpr int kRevRows = 4;          // partners' rows whose loads are in flight together
 constexpr int kUnionRounds = 4;      // shell rounds whose partner loads are in flight together
 
 // FINE: fine-grid positions, general cells possible; otherwise fixed-point
 // positions of orthorhombic cells, with no general-cell code.
 template <bool FINE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 5))) void k_union(const double *__restrict__ pos, const float4 *__restrict__ pos4,
-                                               const double *__restrict__ cen, const float *__restrict__ spr, int P,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_union(const double *__restrict__ pos, const float4 *__restrict__ pos4,
+                                               const double *__restrict__ cen, const float *__restrict__ spr,
+                                               const float4 *__restrict__ cen4, int P,
                                                int N, int S, int lg, const int32_t *__restrict__ atom_sys,
                                                const SysGeom *__restrict__ geom, CutTest cR, CutTest cA,
                                                int32_t *__restrict__ candR, int32_t *__restrict__ offR,
@@ -680,7 +696,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 
                                                int32_t *__restrict__ revA)
 {
     const int lane = threadIdx.x & 63, G = 1 << lg, CPW = 64 >> lg;
-    const int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    // wave-uniform, also to the compiler: the atom's data come by scalar loads
+    const int i = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const int kind = blockIdx.y;   // 0: radial list, 1: angular list
     if (i >= N) return;            // whole wavefront
     if (dev_global(grid)->rebuild) {
@@ -698,29 +715,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 
             // smaller keys in j's row, counted in its unsorted staging copy
             // (no other row need be sorted yet); -1 if i is missing (only
             // when j's row overflowed).  The whole wavefront scans each
-            // partner's row (contiguous loads), one candidate after another;
-            // lane k % 64 keeps slot k's result for one store per 64 slots.
+            // partner's row (contiguous loads), the first 64 entries of
+            // kRevRows partners in flight together; lane k % 64 keeps slot
+            // k's result for one store per 64 slots.
             const int ti = types[i] & 3;
             const int32_t wi = (int32_t)(((uint32_t)i << 2) | (uint32_t)ti);
             const uint32_t ki = cand_key(wi);
             for (int k0 = 0; k0 < n; k0 += 64) {
                 const int kn = min(64, n - k0);
                 const int jl = lane < kn ? (srow[k0 + lane] >> 2) : i;   // the partners of these 64 slots
+                const int nl = min(lenA[jl], capA);                      // and their rows' lengths
                 int res = -1;
-                for (int kk = 0; kk < kn; ++kk) {
-                    const int j = __builtin_amdgcn_readlane(jl, kk);
-                    const int nj = min(lenA[j], capA);
-                    const int32_t *rj = candAs + (size_t)j * capA;
-                    int r = 0;
-                    bool found = false;
-                    for (int f = lane; f < nj; f += 64) {
-                        const int32_t w = rj[f];
-                        r += cand_key(w) < ki;
-                        found |= w == wi;
+                for (int kk = 0; kk < kn; kk += kRevRows) {
+                    int nj[kRevRows];
+                    const int32_t *rj[kRevRows];
+                    int32_t w[kRevRows];
+#pragma unroll
+                    for (int u = 0; u < kRevRows; ++u) {
+                        const int q = min(kk + u, kn - 1);
+                        nj[u] = __builtin_amdgcn_readlane(nl, q);
+                        rj[u] = candAs + (size_t)__builtin_amdgcn_readlane(jl, q) * capA;
+                        w[u] = lane < nj[u] ? rj[u][lane] : 0;
                     }
-                    for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o);
-                    const bool any = __ballot(found) != 0;
-                    if (lane == kk) res = any ? r : -1;
+#pragma unroll
+                    for (int u = 0; u < kRevRows; ++u) {
+                        int r = __popcll(__ballot(lane < nj[u] && cand_key(w[u]) < ki));
+                        uint64_t found = __ballot(lane < nj[u] && w[u] == wi);
+                        for (int f = 64; f < nj[u]; f += 64) {
+                            const int32_t v = f + lane < nj[u] ? rj[u][f + lane] : 0;
+                            r += __popcll(__ballot(f + lane < nj[u] && cand_key(v) < ki));
+                            found |= __ballot(f + lane < nj[u] && v == wi);
+                        }
+                        if (lane == kk + u) res = found ? r : -1;
+                    }
                 }
                 if (lane < kn) revA[(size_t)i * capA + k0 + lane] = res;
             }
@@ -735,8 +762,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 
     const bool tri = FINE && g.tri;
     const uint64_t gmask = (G == 64) ? ~0ull : ((1ull << G) - 1ull);
     const uint64_t full = (P == 64) ? ~0ull : ((1ull << P) - 1ull);
-    const double ci0 = cen[3 * (size_t)i], ci1 = cen[3 * (size_t)i + 1], ci2 = cen[3 * (size_t)i + 2];
-    const double si = (double)spr[i];
 
     const int cap = kind ? capA : capR;
     const int32_t *row = (kind ? candA : candR) + (size_t)i * cap;
@@ -746,6 +771,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 
     int32_t *uend = (kind ? uendA : uendR) + (size_t)i * kMaxSpecies;
     const CutTest c = kind ? cA : cR;
     const double rc = sqrt(c.rc2);
+    const float rcf = (float)rc;
     // batches of 64 row entries run across the species blocks (the row is
     // sorted by species, so the kept entries stay in blocks); each species'
     // kept count gives the block ends
@@ -758,56 +784,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FINE ? 4 : 
             const bool kin = k < kend;
             const int32_t wrow = kin ? row[k] : 0;
             const int j = kin ? wrow >> 2 : i;
-            double dv[3] = {cen[3 * (size_t)j] - ci0, cen[3 * (size_t)j + 1] - ci1, cen[3 * (size_t)j + 2] - ci2};
-            mic_vec(dv, g, tri);
             // d + s < rc - eps and d - s > rc + eps, on squares
-            const double d2 = dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2];
-            const double sp = si + (double)spr[j];
-            const double lo = rc - kShellEps - sp, hi = rc + kShellEps + sp;
-            const bool all_in = kin && lo > 0.0 && d2 < lo * lo;
-            const bool shell = kin && !all_in && !(d2 > hi * hi);
-            int mlo = 0, mhi = 0;
-            uint64_t rem = __ballot(shell);
-            while (rem) {
-                // kUnionRounds rounds of the next CPW shell candidates (one
-                // per group of G lanes), their partners' positions loaded
-                // together; rounds past the last candidate load lane 0's
-                // partner and test nothing
-                uint64_t take[kUnionRounds];
-                int nq[kUnionRounds], jq[kUnionRounds];
+            bool all_in, out;
+            if (FINE) {
+                double dv[3];
 #pragma unroll
-                for (int u = 0; u < kUnionRounds; ++u) {
-                    take[u] = rem;
-                    int my = 0, n = 0;
-                    for (int q = 0; q < CPW && rem; ++q) {
-                        const int sq = __builtin_ctzll(rem);
-                        rem &= rem - 1;
-                        if (q == cg) my = sq;
-                        n = q + 1;
-                    }
-                    nq[u] = n;
-                    jq[u] = __shfl(j, my, 64);
-                }
+                for (int d = 0; d < 3; ++d) dv[d] = cen[3 * (size_t)j + d] - cen[3 * (size_t)i + d];
+                mic_vec(dv, g, tri);
+                const double d2 = dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2];
+                const double sp = (double)spr[i] + (double)spr[j];
+                const double lo = rc - kShellEps - sp, hi = rc + kShellEps + sp;
+                all_in = lo > 0.0 && d2 < lo * lo;
+                out = d2 > hi * hi;
+            } else {
+                const float4 cj = cen4[j], c4i = cen4[i];
+                float dx, dy, dz;
+                fixed_pair(cj, c4i, g.fx, dx, dy, dz);
+                const float d2 = dx * dx + dy * dy + dz * dz;
+                const float sp = c4i.w + cj.w;
+                const float lo = rcf - (float)kShellEps - sp, hi = rcf + (float)kShellEps + sp;
+                all_in = lo > 0.0f && d2 < lo * lo;
+                out = d2 > hi * hi;
+            }
+            all_in = all_in && kin;
+            const bool shell = kin && !all_in && !out;
+            // the shell candidates' partners in rank order, one per lane (a
+            // permutation: the other lanes follow behind)
+            const uint64_t bs = __ballot(shell);
+            const int ns = __popcll(bs);
+            const int rk = __builtin_amdgcn_mbcnt_hi((uint32_t)(bs >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bs, 0));
+            const int jc = __builtin_amdgcn_ds_permute((shell ? rk : ns + lane - rk) * 4, j);
+            int clo = 0, chi = 0;   // mask of the candidate of rank `lane`
+            for (int u0 = 0; u0 * CPW < ns; u0 += kUnionRounds) {
+                // kUnionRounds rounds of CPW candidates (one per group of G
+                // lanes), their partners' positions loaded together
+                int jq[kUnionRounds];
                 float4 pj[kUnionRounds];
+#pragma unroll
+                for (int u = 0; u < kUnionRounds; ++u) jq[u] = __shfl(jc, min((u0 + u) * CPW + cg, ns - 1), 64);
 #pragma unroll
                 for (int u = 0; u < kUnionRounds; ++u) pj[u] = pos4[(size_t)jq[u] * P + bb];
 #pragma unroll
                 for (int u = 0; u < kUnionRounds; ++u) {
                     const float r2f = packed_r2<FINE>(pj[u], pi, g);
-                    const bool in = cg < nq[u] && bead_ok && pair_within(r2f, c, pb, i, jq[u], g, tri);
-                    const uint64_t m = __ballot(in);
-                    uint64_t tk = take[u];
-                    for (int q = 0; q < nq[u]; ++q) {
-                        const int sq = __builtin_ctzll(tk);
-                        tk &= tk - 1;
-                        const uint64_t gm = (m >> (q * G)) & gmask;
-                        if (lane == sq) {
-                            mlo = (int)(uint32_t)gm;
-                            mhi = (int)(uint32_t)(gm >> 32);
-                        }
+                    const bool in = (u0 + u) * CPW + cg < ns && bead_ok && pair_within(r2f, c, pb, i, jq[u], g, tri);
+                    const uint64_t m = (__ballot(in) >> ((lane & (CPW - 1)) << lg)) & gmask;
+                    if (lane >> (6 - lg) == u0 + u) {
+                        clo = (int)(uint32_t)m;
+                        chi = (int)(uint32_t)(m >> 32);
                     }
                 }
             }
+            const int mlo = __shfl(clo, rk & 63, 64), mhi = __shfl(chi, rk & 63, 64);   // back to the candidate's lane
             const uint64_t mask = all_in ? full : (shell ? (((uint64_t)(uint32_t)mhi << 32) | (uint32_t)mlo) : 0ull);
             const bool keep = mask != 0ull;
             const uint64_t bal = __ballot(keep);
@@ -1001,7 +1029,7 @@ extern "C" int32_t neighbor_build_batched(const nep_model *m, nep_nlist *nl, con
         const int nblk = div_up(N * kCenLanes, kBlock);
         hipLaunchKernelGGL(k_centroid, dim3(nblk), dim3(kBlock), 0, s, pos, types, nl->atom_sys, P, N, nl->S,
                            nl->cen, nl->spr, nl->cen_ref, nl->geom, nl->grid, nl->status,
-                           reinterpret_cast<float4 *>(nl->pos4), nl->cmax);
+                           reinterpret_cast<float4 *>(nl->pos4), reinterpret_cast<float4 *>(nl->cen4), nl->cmax);
         hipLaunchKernelGGL(k_decide, dim3(1), dim3(kDecideBlock), 0, s, nl->geom, nl->nsys, m->hp.rc_radial,
                            m->hp.rc_angular, nl->skin, force ? 1 : 0, nl->grid, nl->status, nl->cen, N, nl->atom_sys,
                            nl->ncell_total, nl->cell_cnt, nl->cell_start, nl->cell_atoms, nl->cmax, nblk);
@@ -1021,8 +1049,9 @@ extern "C" int32_t neighbor_build_batched(const nep_model *m, nep_nlist *nl, con
         const CutTest cA{(float)rA2, margin, rA2};
         auto kern = nl->fine_pos ? k_union<true> : k_union<false>;
         hipLaunchKernelGGL(kern, dim3(div_up(N, kBlock / 64), 2), dim3(kBlock), 0, s, pos,
-                           reinterpret_cast<const float4 *>(nl->pos4), nl->cen, nl->spr, P, N, nl->S, lg, nl->atom_sys, nl->geom, cR,
-                           cA, nl->candR, nl->offR, nl->candA, nl->offA, nl->candRs, nl->candAs, nl->lenR, nl->lenA,
+                           reinterpret_cast<const float4 *>(nl->pos4), nl->cen, nl->spr,
+                           reinterpret_cast<const float4 *>(nl->cen4), P, N, nl->S, lg, nl->atom_sys, nl->geom, cR, cA,
+                           nl->candR, nl->offR, nl->candA, nl->offA, nl->candRs, nl->candAs, nl->lenR, nl->lenA,
                            nl->capR, nl->capA, nl->uniR, nl->umR,
                            nl->uendR, nl->uniA, nl->umA, nl->uendA, nl->status, nl->grid, types, nl->revA);
     }
