@@ -684,8 +684,8 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
     if (e == hipSuccess) e = dalloc(&nl->pos4, 4 * PN);
     if (e == hipSuccess) e = dalloc(&nl->cell_atoms, Nn);
     if (e == hipSuccess) e = dalloc(&nl->grid, 16 + kDevSysWords * (size_t)nsys);
-    if (e == hipSuccess) e = dalloc(&nl->status, 8);
-    if (e == hipSuccess) e = hipMemset(nl->status, 0, 8 * sizeof(uint32_t));
+    if (e == hipSuccess) e = dalloc(&nl->status, kStatusSlots * kStatusWords);
+    if (e == hipSuccess) e = hipMemset(nl->status, 0, kStatusSlots * kStatusWords * sizeof(uint32_t));
     // pair terms start at zero: a slot that a step with truncated rows leaves
     // unwritten then holds a finite stale value, never uninitialised bits
     if (e == hipSuccess && PN) e = hipMemset(nl->pairbuf, 0, sizeof(float) * 4 * PN * capA);
@@ -739,9 +739,11 @@ extern "C" int32_t nep_nlist_view(const nep_nlist *nl, nep_nlist_layout *out)
 extern "C" int32_t nep_nlist_poll(nep_nlist *nl, nep_nlist_status *out, int32_t clear, hipStream_t s)
 {
     if (!nl || !out) return fail(NEP_ERR_INVALID_ARG, "nep_nlist_poll: null argument");
-    uint32_t h[8];
+    uint32_t h[kStatusSlots * kStatusWords];
     NEP_HIP(hipStreamSynchronize(s));
     NEP_HIP(hipMemcpy(h, nl->status, sizeof h, hipMemcpyDeviceToHost));
+    for (int k = 1; k < kStatusSlots; ++k)
+        for (int w : {1, 2, 3, 6}) h[w] = std::max(h[w], h[k * kStatusWords + w]);
     out->flags = h[0];
     out->max_union_radial = (int32_t)h[1];
     out->max_union_angular = (int32_t)h[2];
@@ -752,7 +754,7 @@ extern "C" int32_t nep_nlist_poll(nep_nlist *nl, nep_nlist_status *out, int32_t 
     out->bead_spread = spread;
     out->rebuilds = (int32_t)h[5];
     if (clear) {
-        fill_u32(nl->status, 0u, 8, s);
+        fill_u32(nl->status, 0u, kStatusSlots * kStatusWords, s);
         NEP_HIP(hipGetLastError());
         NEP_HIP(hipStreamSynchronize(s));
     }

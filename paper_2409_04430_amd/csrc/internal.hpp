@@ -119,6 +119,12 @@ bool cell_info(const double box[9], CellInfo &c);
 // (NEP_OK, or the error code after fail()).
 int32_t check_offsets(int32_t nsys, const int32_t *off, const char *who);
 
+namespace nep {
+// Status record of the lists: kStatusSlots copies of kStatusWords words, one
+// 64-byte line each.
+constexpr int kStatusSlots = 32, kStatusWords = 16;
+}  // namespace nep
+
 struct nep_nlist {
     int P = 0, N = 0, S = 0;
     int capR = 0, capA = 0;       // candidate row capacities per atom (radial, angular radius)
@@ -170,9 +176,10 @@ struct nep_nlist {
     int32_t *cell_cnt = nullptr, *cell_start = nullptr, *cell_atoms = nullptr;
     double rc_built[2] = {0.0, 0.0};   // cutoffs (radial, angular) of the last neighbor_build
     uint32_t *grid = nullptr;     // device-chosen grid record: 16 global words + kDevSysWords per system
-    uint32_t *status = nullptr;   // [0] flags, [1] max radial union, [2] max angular union,
+    uint32_t *status = nullptr;   // [kStatusSlots][kStatusWords]: [0] flags, [1] max radial union, [2] max angular union,
                                   // [3] max radial candidates, [4] spread (float bits), [5] rebuilds,
-                                  // [6] max angular candidates
+                                  // [6] max angular candidates; the maxima spread over the slots
+                                  // (status_slot), the other words in slot 0
 };
 
 // Per-(system, bead) energy and virial sums over the force kernels'

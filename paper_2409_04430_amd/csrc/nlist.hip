@@ -82,12 +82,19 @@ __device__ __forceinline__ float wave_max_f(float v)
 
 // Sticky maximum of a status word: thousands of wavefronts updating one
 // address serialise in the L2, so the atomic is issued only when v exceeds
-// the stored value.  The words only grow between the host's clears, and a
+// the stored value, on the slot of the workgroup (after a clear the first
+// wavefronts all raise the word: 3072 of them on one address took 22 of the
+// 28 us of the union lists of 1536 atoms).  The words only grow between the host's clears, and a
 // kernel never sees a value older than the last clear, so a stale read can
 // only cost an extra atomic, never lose a maximum.
 __device__ __forceinline__ void raise_max(uint32_t *word, uint32_t v)
 {
     if (v > __atomic_load_n(word, __ATOMIC_RELAXED)) atomicMax(word, v);
+}
+
+__device__ __forceinline__ uint32_t *status_slot(uint32_t *status)
+{
+    return status + (blockIdx.x % kStatusSlots) * kStatusWords;
 }
 
 // Centroid of each atom's ring polymer, its largest bead distance D_i and
@@ -635,8 +642,8 @@ __global__ __launch_bounds__(256) void k_candidates(const double *__restrict__ c
             cen_ref[3 * i] = ci[0];
             cen_ref[3 * i + 1] = ci[1];
             cen_ref[3 * i + 2] = ci[2];
-            raise_max(&status[3], (uint32_t)cR);
-            raise_max(&status[6], (uint32_t)cA);
+            raise_max(&status_slot(status)[3], (uint32_t)cR);
+            raise_max(&status_slot(status)[6], (uint32_t)cA);
             if (cR > capR || cA > capA) {
                 atomicOr(&status[0], (uint32_t)NEP_FLAG_NEIGHBOR_OVERFLOW);
                 atomicOr(&dg->rows_overflow, 1u);
@@ -855,7 +862,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             run += cntS[t];
             uend[t] = run;
         }
-        raise_max(&status[1 + kind], (uint32_t)cnt);
+        raise_max(&status_slot(status)[1 + kind], (uint32_t)cnt);
     }
 }
 
