@@ -395,7 +395,7 @@ template <bool TRI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_d3_cnforce(D3Args a)
 {
     __shared__ double t[kTab];
-    __shared__ double lds[256];
+    __shared__ SumLds<9> lds;
     load_tab(a, t);
     int i, b;
     const bool ok = d3_lane(a, i, b);
@@ -470,8 +470,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
     const int nblk = gridDim.x;
     const int comp[9] = {0, 3, 4, 3, 1, 5, 4, 5, 2};
-    for (int c = 0; c < 9; ++c)
-        bead_block_sum(ok ? Wv[comp[c]] : 0.0, lds, P, a.lg, a.partW1 + (size_t)c * nblk + blockIdx.x, 9 * nblk);
+    double Wo[9];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) Wo[c] = Wv[comp[c]];
+    bead_block_sums(Wo, ok, lds, P, a.lg, a.partW1 + blockIdx.x, nblk, 9 * nblk);
 }
 
 // One workgroup per (bead, component c): c = 0 energy, 1..9 virial; partial

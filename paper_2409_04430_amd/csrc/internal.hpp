@@ -276,15 +276,67 @@ __device__ __forceinline__ void reduce_output(const PendingReduce &r, int o, int
     double acc = 0.0;
     int k = k0 + t;
     if (r.rowp) {
+        // tile sums in the order of bead_block_sums: chunks of A atoms (one
+        // wavefront of the general kernels) pairwise, the tile's up to four
+        // chunks one after another
         const size_t PN = (size_t)r.P * r.N;
-        const float *va = r.rowp + (size_t)c * PN + (size_t)b * r.N, *vr = va + 9 * PN;
-        for (; k < k1; k += 64) {
-            const int a0 = r.tile_atom0[k], a1 = r.tile_atom1[k];
-            double sa = 0.0, sr = 0.0;
-            for (int i = a0; i < a1; ++i) sa += (double)va[i];
-            if (c)
-                for (int i = a0; i < a1; ++i) sr += (double)vr[i];
-            acc += sa + sr;
+        const float *va = r.rowp + (size_t)c * PN + (size_t)b * r.N, *vr = va + (c ? 9 * PN : 0);
+        int A = 64;
+        while ((64 / A) < r.P) A >>= 1;
+        const auto tree = [](const float (&v)[8]) {
+            const double x0 = (double)v[0] + (double)v[4], x1 = (double)v[1] + (double)v[5];
+            const double x2 = (double)v[2] + (double)v[6], x3 = (double)v[3] + (double)v[7];
+            return (x0 + x2) + (x1 + x3);
+        };
+        if (A <= 8) {   // one lane per tile
+            for (; k < k1; k += 64) {
+                const int a1 = r.tile_atom1[k];
+                double sa = 0.0, sr = 0.0;
+                for (int i0 = r.tile_atom0[k]; i0 < a1; i0 += A) {
+                    float v[8], w[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const bool in = u < A && i0 + u < a1;
+                        v[u] = in ? va[i0 + u] : 0.0f;
+                        w[u] = in && c ? vr[i0 + u] : 0.0f;
+                    }
+                    sa += tree(v);
+                    sr += tree(w);
+                }
+                acc += sa + sr;
+            }
+        } else {
+            // eight lanes per chunk, two tiles at once: each lane adds the
+            // chunk's atoms 8 apart pairwise, the lanes meet by shuffles
+            for (int kk = k0; kk < k1; kk += 2) {
+                const int ck = t >> 3, kt = kk + (ck >> 2);
+                const bool has = kt < k1;
+                const int i0 = has ? r.tile_atom0[kt] + (ck & 3) * A : 0, a1 = has ? r.tile_atom1[kt] : 0;
+                float v[8], w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int q = (t & 7) + 8 * u;
+                    const bool in = q < A && i0 + q < a1;
+                    v[u] = in ? va[i0 + q] : 0.0f;
+                    w[u] = in && c ? vr[i0 + q] : 0.0f;
+                }
+                double xa = tree(v), xr = tree(w);
+                for (int s = 4; s > 0; s >>= 1) {
+                    xa += __shfl_xor(xa, s);
+                    xr += __shfl_xor(xr, s);
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    double sa = 0.0, sr = 0.0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        sa += __shfl(xa, (4 * h + q) * 8);
+                        sr += __shfl(xr, (4 * h + q) * 8);
+                    }
+                    if (kk + h < k1 && t == ((kk + h - k0) & 63)) acc += sa + sr;
+                }
+            }
+            k = k1;
         }
     }
     for (; k + 192 < k1; k += 256) {

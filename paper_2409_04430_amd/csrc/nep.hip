@@ -406,9 +406,10 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
 
     if (valid && a.Eatom) a.Eatom[(size_t)b * a.N + i] = U;
     if (valid && !tok) atomicOr(a.flags, (uint32_t)NEP_FLAG_BAD_TYPE);
-    __shared__ double lds[kBlock];
+    __shared__ SumLds<1> lds;
     // partials bead-major, [P][workgroups]: the reduction reads them contiguously
-    bead_block_sum(valid ? (double)U : 0.0, lds, P, a.lg, a.partE + blockIdx.x, gridDim.x);
+    const float Us[1] = {U};
+    bead_block_sums(Us, valid, lds, P, a.lg, a.partE + blockIdx.x, 0, gridDim.x);
 }
 
 // ------------------------------------------------ pass 2: angular, own ---
@@ -595,10 +596,8 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
             for (int e = 0; e < 9; ++e) wo[e] = 0.5f * Wv[e];
         }
     }
-    __shared__ double lds[kBlock];
-    for (int e = 0; e < 9; ++e)
-        bead_block_sum(valid ? (double)Wv[e] : 0.0, lds, P, a.lg, a.partWa + (size_t)e * gridDim.x + blockIdx.x,
-                       9 * gridDim.x);
+    __shared__ SumLds<9> lds;
+    bead_block_sums(Wv, valid, lds, P, a.lg, a.partWa + blockIdx.x, gridDim.x, 9 * gridDim.x);
 }
 
 // ----------------------------------------- pass 3: radial + combination ---
@@ -748,10 +747,8 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
         }
         if (!(isfinite(gx) && isfinite(gy) && isfinite(gz))) atomicOr(a.flags, (uint32_t)NEP_FLAG_NONFINITE);
     }
-    __shared__ double lds[kBlock];
-    for (int e = 0; e < 9; ++e)
-        bead_block_sum(valid ? (double)Wf[e] : 0.0, lds, P, a.lg, a.partWr + (size_t)e * gridDim.x + blockIdx.x,
-                       9 * gridDim.x);
+    __shared__ SumLds<9> lds;
+    bead_block_sums(Wf, valid, lds, P, a.lg, a.partWr + blockIdx.x, gridDim.x, 9 * gridDim.x);
 }
 
 // Per-(system, bead) energy and virial from the per-workgroup partial sums

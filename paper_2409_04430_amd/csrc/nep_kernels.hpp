@@ -122,18 +122,40 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Per-bead sums over the atoms of a block in a fixed order: thread b < P
-// adds the values of the lanes of bead b and writes out[b * stride].
-__device__ __forceinline__ void bead_block_sum(double v, double *lds, int P, int lg, double *out, int stride)
+// Per-bead sums of NV values over the atoms of a block, in a fixed order:
+// each wavefront's atoms (adjacent groups of 2^lg lanes) pairwise by a
+// butterfly, the wavefronts then one after another; out[e * vstride +
+// b * stride] for value e and bead b < P.  kSumVals values share one barrier
+// pair; the butterflies replace a serial walk over the block's atoms by one
+// lane per bead (256 / 2^lg dependent LDS reads per value).  reduce_output
+// takes the same order from per-row values.
+constexpr int kSumVals = 3;
+template <int NV>
+struct SumLds { double v[(NV < kSumVals ? NV : kSumVals) * kBlock]; };
+template <int NV, typename T>
+__device__ __forceinline__ void bead_block_sums(const T (&v)[NV], bool valid, SumLds<NV> &lds, int P, int lg,
+                                                double *out, size_t vstride, int stride)
 {
-    lds[threadIdx.x] = v;
-    __syncthreads();
-    if ((int)threadIdx.x < P) {
-        double s = 0.0;
-        for (int x = threadIdx.x; x < (int)blockDim.x; x += 1 << lg) s += lds[x];
-        out[(size_t)threadIdx.x * stride] = s;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6, G = 1 << lg;
+    constexpr int NS = NV < kSumVals ? NV : kSumVals;
+#pragma unroll
+    for (int e0 = 0; e0 < NV; e0 += NS) {
+        if (e0) __syncthreads();
+#pragma unroll
+        for (int x = 0; x < NS; ++x) {
+            double s = valid ? (double)v[e0 + x < NV ? e0 + x : NV - 1] : 0.0;
+            for (int o = 32; o >= G; o >>= 1) s += __shfl_xor(s, o);
+            if (lane < G) lds.v[(x * nw + wv) * G + lane] = s;
+        }
+        __syncthreads();
+        for (int x = wv; x < NS; x += nw) {
+            if (lane < P && e0 + x < NV) {
+                double s = 0.0;
+                for (int w = 0; w < nw; ++w) s += lds.v[(x * nw + w) * G + lane];
+                out[(size_t)(e0 + x) * vstride + (size_t)lane * stride] = s;
+            }
+        }
     }
-    __syncthreads();
 }
 
 // Adjoint rows B_i (and the angular sums parked in them) are stored
