@@ -667,7 +667,7 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
     // in the angular force, the longest block of a wavefront more.
     // One allocation and one fill for all of them.
     const size_t slack = (size_t)capA + 16, nR = Nn * capR + slack, nA = Nn * capA + slack;
-    const size_t words = 3 * nR + 3 * nA + 2 * Nn * capA;   // 64-bit masks first
+    const size_t words = 3 * nR + 5 * nA + 2 * Nn * capA;   // 64-bit masks first
     if (e == hipSuccess) e = dalloc(&nl->lists, words);
     if (e == hipSuccess) e = hipMemset(nl->lists, 0, sizeof(int32_t) * words);
     if (e == hipSuccess) {
@@ -675,7 +675,9 @@ extern "C" int32_t nep_nlist_create_batched(const nep_model *m, int32_t P, int32
         nl->umA = nl->umR + nR;
         nl->uniR = reinterpret_cast<int32_t *>(nl->umA + nA);
         nl->uniA = nl->uniR + nR;
-        nl->candA = nl->uniA + nA;
+        nl->uniW = nl->uniA + nA;
+        nl->uniV = nl->uniW + nA;
+        nl->candA = nl->uniV + nA;
         nl->revA = nl->candA + Nn * capA;
     }
     if (e == hipSuccess) e = dalloc(&nl->uendR, Nn * kMaxSpecies);

@@ -63,7 +63,7 @@ struct D3Args {
     int N, P, lg, S;
     int lgc;                     // dispersion pass: 2^lgc lanes per atom, one bead chunk each
     const SysGeom *geom;
-    const int32_t *candA, *uniR, *uendR, *uniA, *uendA;
+    const int32_t *uniR, *uendR, *uniW, *uendA;
     const uint64_t *umR, *umA;
     int capR, capA;
     const double *tab;
@@ -216,9 +216,8 @@ __global__ __launch_bounds__(256) void k_d3_cn(D3Args a)
     const SysGeom &g = a.geom[0];
     const int P = a.P, ti = a.types[i] & 3;
     const double *ri = a.posT + ((size_t)i * P + b) * 3;
-    const int32_t *uA = a.uniA + (size_t)i * a.capA;
+    const int32_t *uW = a.uniW + (size_t)i * a.capA;
     const uint64_t *mA = a.umA + (size_t)i * a.capA;
-    const int32_t *row = a.candA + (size_t)i * a.capA;
     const int n = a.uendA[(size_t)i * kMaxSpecies + a.S - 1];
     const double xi = ri[0], yi = ri[1], zi = ri[2];
     const double Ri = t[kTRcov + ti], kk = a.k1 * a.k2;
@@ -232,10 +231,8 @@ __global__ __launch_bounds__(256) void k_d3_cn(D3Args a)
             const int e = min(e0 + k, n - 1);
             const uint64_t m = mA[e];
             mm[k] = e0 + k < n ? m : 0ull;
-            w[k] = uA[e];
+            w[k] = uW[e];
         }
-#pragma unroll
-        for (int k = 0; k < kD3Batch; ++k) w[k] = row[w[k]];
         double pj[kD3Batch][3];
 #pragma unroll
         for (int k = 0; k < kD3Batch; ++k) {
@@ -404,9 +401,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const double *ri = a.posT + ((size_t)i * P + b) * 3;
     const double xi = ri[0], yi = ri[1], zi = ri[2];
     const double dEi = a.dedcn[(size_t)i * P + b];
-    const int32_t *uA = a.uniA + (size_t)i * a.capA;
+    const int32_t *uW = a.uniW + (size_t)i * a.capA;
     const uint64_t *mA = a.umA + (size_t)i * a.capA;
-    const int32_t *row = a.candA + (size_t)i * a.capA;
     const int n = ok ? a.uendA[(size_t)i * kMaxSpecies + a.S - 1] : 0;
     const double Ri = t[kTRcov + ti], kk = a.k1 * a.k2;
     double fx = 0.0, fy = 0.0, fz = 0.0;
@@ -419,10 +415,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const int e = min(e0 + k, n - 1);
             const uint64_t m = mA[e];
             mm[k] = e0 + k < n ? m : 0ull;
-            w[k] = uA[e];
+            w[k] = uW[e];
         }
-#pragma unroll
-        for (int k = 0; k < kD3Batch; ++k) w[k] = row[w[k]];
         double pj[kD3Batch][3], dEj[kD3Batch];
 #pragma unroll
         for (int k = 0; k < kD3Batch; ++k) {
@@ -707,7 +701,7 @@ extern "C" int32_t nep_d3_compute(const nep_d3 *d, nep_nlist *nl, nep_d3_ws *w, 
     a.types = types;
     a.N = N; a.P = P; a.lg = w->lg; a.lgc = w->lgc; a.S = d->S;
     a.geom = nl->geom;
-    a.candA = nl->candA; a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA; a.uendA = nl->uendA;
+    a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniW = nl->uniW; a.uendA = nl->uendA;
     a.umR = nl->umR; a.umA = nl->umA; a.capR = nl->capR; a.capA = nl->capA;
     a.tab = d->dev;
     a.s6 = d->s6; a.s8 = d->s8; a.k1 = d->k1; a.k2 = d->k2; a.k3 = d->k3;

@@ -149,7 +149,7 @@ struct nep_nlist {
     float *cen4 = nullptr;        // [N][4] centroid in the fixed-point form and its spread (systems of that form)
     float *cmax = nullptr;        // [ceil(kCenLanes N / kBlock)][2] per-workgroup maxima of the centroid kernel
     double *cen_ref = nullptr;    // [N][3] centroids at the last rebuild
-    int32_t *lists = nullptr;     // one allocation: umR, umA, uniR, uniA, candA, revA
+    int32_t *lists = nullptr;     // one allocation: umR, umA, uniR, uniA, uniW, uniV, candA, revA
     int32_t *candR = nullptr;     // [N][capR] entries (j << 2) | species(j), sorted by (species, j)
     int32_t *candRs = nullptr;    // [N][capR] the same rows unsorted, as the candidate search leaves them
     int32_t *candAs = nullptr;    // [N][capA] the angular rows unsorted
@@ -165,6 +165,7 @@ struct nep_nlist {
     uint64_t *umR = nullptr;      // [N][capR] bit b: inside the radial cutoff in bead b
     int32_t *uendR = nullptr;     // [N][4]
     int32_t *uniA = nullptr;      // [N][capA] angular slots k
+    int32_t *uniW = nullptr, *uniV = nullptr;   // [N][capA] the entries' candidate words j << 2 | type and reverse slots
     uint64_t *umA = nullptr;      // [N][capA] bit b: inside the angular cutoff in bead b
     int32_t *uendA = nullptr;     // [N][4]
     // Angular pair terms dU_j/dr_ji at the receiving atom i's angular slot of j: [N][capA][P] xyz + pad.

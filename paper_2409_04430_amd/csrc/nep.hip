@@ -149,9 +149,8 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
         // the accumulators of one pass fit the registers), each pass's q
         // entries formed and its A parked before the next
         constexpr int NG = NA1 > 5 ? (NA1 + 2) / 3 : NA1;
-        const int32_t *uA = a.uniA + (size_t)i * a.capA;
+        const int32_t *uW = a.uniW + (size_t)i * a.capA;
         const uint64_t *mA = a.umA + (size_t)i * a.capA;
-        const int32_t *rowA = a.candA + (size_t)i * a.capA;
 #pragma unroll
         for (int n0 = 0; n0 < NA1; n0 += NG) {
         float A[NG][kNumSH];
@@ -173,23 +172,20 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                 for (int q2 = 0; q2 < KA1; ++q2) acc += c[n * KA1 + q2];
                 cs[g] = acc;
             }
-            // batches of kBatch entries: slots, then partners, then their
-            // positions, each level's loads in flight together (entries past
-            // the block end masked off)
+            // batches of kBatch entries: partners, then their positions,
+            // each level's loads in flight together (entries past the block
+            // end masked off)
             for (int sb = s0; sb < s1; sb += kBatch) {
                 // coefficients through scalar loads, which do not wait on the gathers
                 const cf32p cl = launder(c);
-                int kq[kBatch];
                 bool in[kBatch];
                 float4 pj[kBatch];
-                const idx_run<kBatch> ku = *reinterpret_cast<const idx_run<kBatch> *>(uA + sb);
+                const idx_run<kBatch> jj = *reinterpret_cast<const idx_run<kBatch> *>(uW + sb);
                 const mask_run<kBatch> mm = *reinterpret_cast<const mask_run<kBatch> *>(mA + sb);
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) in[u] = (sb + u < s1) & ((mm.v[u] & bit) != 0);
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) kq[u] = rowA[(uint32_t)ku.v[u]] >> 2;
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) pj[u] = *row_at(p4b, kq[u], pstride);
+                for (int u = 0; u < kBatch; ++u) pj[u] = *row_at(p4b, jj.v[u] >> 2, pstride);
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) keep(pj[u]);
 #pragma unroll
@@ -448,10 +444,8 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
     float4 *pairb = a.pairbuf + b;
     const float4 pi = *row_at(p4b, i, pstride);
     const float *shc = prm + a.osh;
-    const int32_t *uA = a.uniA + (size_t)i * a.capA;
+    const int32_t *uW = a.uniW + (size_t)i * a.capA, *uV = a.uniV + (size_t)i * a.capA;
     const uint64_t *mA = a.umA + (size_t)i * a.capA;
-    const int32_t *rowA = a.candA + (size_t)i * a.capA;
-    const int32_t *rvA = a.revA + (size_t)i * a.capA;
     float Fx = 0.0f, Fy = 0.0f, Fz = 0.0f;
     float Wv[9];
 #pragma unroll
@@ -506,32 +500,27 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
             cmax = __builtin_amdgcn_readfirstlane(cmax);
             const float *cij = prm + a.oA + (tc * S + t) * NA1 * KA1;
             for (int sb = 0; sb < cmax; sb += kBatchAng) {
-                // the batch's slots, partners, positions and reverse slots,
-                // each level's loads in flight together (a lane past the end
+                // the batch's partners, reverse slots and positions, each
+                // level's loads in flight together (a lane past the end
                 // of its block reads entries that are valid but masked off;
                 // its position stays below the longest block of the
                 // wavefront, which the arrays' slack covers)
-                int jq[kBatchAng], rq[kBatchAng];
                 bool aq[kBatchAng];
                 float4 pq[kBatchAng];
-                const idx_run<kBatchAng> ku = *reinterpret_cast<const idx_run<kBatchAng> *>(uA + s0 + sb);
+                const idx_run<kBatchAng> jq = *reinterpret_cast<const idx_run<kBatchAng> *>(uW + s0 + sb);
+                const idx_run<kBatchAng> rq = *reinterpret_cast<const idx_run<kBatchAng> *>(uV + s0 + sb);
                 const mask_run<kBatchAng> mm = *reinterpret_cast<const mask_run<kBatchAng> *>(mA + s0 + sb);
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) aq[u] = (sb + u < cnt) & ((mm.v[u] & bit) != 0);
 #pragma unroll
-                for (int u = 0; u < kBatchAng; ++u) {
-                    jq[u] = rowA[(uint32_t)ku.v[u]] >> 2;
-                    rq[u] = rvA[(uint32_t)ku.v[u]];
-                }
-#pragma unroll
-                for (int u = 0; u < kBatchAng; ++u) pq[u] = *row_at(p4b, jq[u], pstride);
+                for (int u = 0; u < kBatchAng; ++u) pq[u] = *row_at(p4b, jq.v[u] >> 2, pstride);
                 if (!formed) get_adjoints();
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) keep(pq[u]);
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) {
                 const cf32p cij_l = launder(cij);
-                const int j = jq[u];
+                const int j = jq.v[u] >> 2;
                 const bool act = aq[u];
                 if (__ballot(act) == 0) continue;
                 float dx, dy, dz;
@@ -570,7 +559,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                 float px, py, pz;
                 pair_term(ux, uy, uz, rinv, sY, gx, gy, gz, px, py, pz);
                 if (act) {
-                    const int rk = rq[u];
+                    const int rk = rq.v[u];
                     if (rk >= 0)
                         *const_cast<float4 *>(row_at(row_at(pairb, j, (uint32_t)a.capA * pstride), rk, pstride)) =
                             make_float4(px, py, pz, 0.0f);
@@ -689,9 +678,8 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
         Wf[7] = Wf[5];
 
         // reverse angular terms: F_i -= dU_j/dr_ji for every angular neighbour j
-        const int32_t *uA = a.uniA + (size_t)i * a.capA;
+        const int32_t *uA = a.uniA + (size_t)i * a.capA, *uW = a.uniW + (size_t)i * a.capA;
         const uint64_t *mA = a.umA + (size_t)i * a.capA;
-        const int32_t *rowA = a.candA + (size_t)i * a.capA;
         const float4 *pbuf = row_at(a.pairbuf + b, i, (uint32_t)a.capA * pstride);
         const int nA = a.uendA[(size_t)i * kMaxSpecies + S - 1];
         float gx = 0.0f, gy = 0.0f, gz = 0.0f;
@@ -719,7 +707,7 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
                 for (int u = 0; u < kBatchRev; ++u) {
                     if (!in[u]) continue;
                     float dx, dy, dz;
-                    pair_vec<FINE>(*row_at(p4b, rowA[(uint32_t)kk.v[u]] >> 2, pstride), pi, lm, dx, dy, dz);
+                    pair_vec<FINE>(*row_at(p4b, uW[sb + u] >> 2, pstride), pi, lm, dx, dy, dz);
                     const float4 dd = d[u];
                     // reverse half of the per-atom split: +1/2 r_ij (x) dU_j/dr_ji
                     const float hx = 0.5f * dx, hy = 0.5f * dy, hz = 0.5f * dz;
@@ -851,7 +839,8 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     a.geom = nl->geom; a.tile_atom0 = ws->tile_atom0; a.tile_atom1 = ws->tile_atom1; a.tile_sys = ws->tile_sys;
     a.rcRinv = (float)(1.0 / h.rc_radial); a.rcAinv = (float)(1.0 / h.rc_angular);
     a.kappa4 = (float)(-4.5 * std::sqrt(2.0 / 35.0) * std::pow(5.0 / (4.0 * M_PI), 1.5));
-    a.candA = nl->candA; a.revA = nl->revA; a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA;
+    a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA;
+    a.uniW = nl->uniW; a.uniV = nl->uniV;
     a.umR = nl->umR; a.umA = nl->umA;
     a.uendA = nl->uendA; a.capR = nl->capR; a.capA = nl->capA;
     a.pairbuf = reinterpret_cast<float4 *>(nl->pairbuf);

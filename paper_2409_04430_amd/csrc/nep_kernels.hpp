@@ -19,8 +19,9 @@ struct NepArgs {
     const int32_t *tile_atom0, *tile_atom1, *tile_sys;   // per workgroup: atom range and system
     float rcRinv, rcAinv;
     float kappa4;
-    // candidate rows and union lists of the neighbour handle
-    const int32_t *candA, *revA, *uniR, *uendR, *uniA, *uendA;
+    // union lists of the neighbour handle
+    const int32_t *uniR, *uendR, *uniA, *uendA;
+    const int32_t *uniW, *uniV;  // candidate words (j << 2 | type) and reverse slots of the angular union entries
     const uint64_t *umR, *umA;   // bead masks of the union entries
     int capR, capA;
     float4 *pairbuf;     // [N][capA][P] dU_j/dr_ji at the receiving atom's angular slot of j

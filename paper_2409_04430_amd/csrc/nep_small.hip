@@ -126,9 +126,8 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
     wave_lds_sync();
 
     // ---- angular sums: owner lane of entry (n, m) adds g_n p_m over the neighbours
-    const int32_t *uA = a.uniA + (size_t)i * a.capA;
+    const int32_t *uW = a.uniW + (size_t)i * a.capA;
     const uint64_t *mA = a.umA + (size_t)i * a.capA;
-    const int32_t *rowA = a.candA + (size_t)i * a.capA;
     const int nA = uendA[S - 1];
     {
         float A[NACC];
@@ -148,7 +147,7 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
 #pragma unroll
             for (int m = 0; m < kNumSH; ++m) Y[m] = 0.0f;
             if (e < nA && ((mA[e] >> b) & 1u)) {
-                const int32_t w = rowA[uA[e]];
+                const int32_t w = uW[e];
                 float dx, dy, dz;
                 pair_vec<true>(*row_at(p4b, w >> 2, pstride), pi, lm, dx, dy, dz);
                 const float r2 = norm2(dx, dy, dz);
@@ -287,7 +286,7 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
     }
 
     // ---- angular pair terms: per lane one neighbour, owner lanes 0..2 force, 3..11 virial
-    const int32_t *rvA = a.revA + (size_t)i * a.capA;
+    const int32_t *uV = a.uniV + (size_t)i * a.capA;
     float4 *pairb = a.pairbuf + b;
     const int we = lane - 3, wa = we / 3, wb = we - 3 * wa;
     float acc = 0.0f;
@@ -296,9 +295,8 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
         const bool act = e < nA && ((mA[e < nA ? e : 0] >> b) & 1u);
         float px = 0.0f, py = 0.0f, pz = 0.0f, dx = 1.0f, dy = 0.0f, dz = 0.0f;
         if (act) {
-            const int slot = uA[e];
-            const int32_t w = rowA[slot];
-            const int rk = rvA[slot], j = w >> 2, t = w & 3;
+            const int32_t w = uW[e];
+            const int rk = uV[e], j = w >> 2, t = w & 3;
             pair_vec<true>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
             const float r2 = norm2(dx, dy, dz);
             const float rinv = __builtin_amdgcn_rsqf(r2);
@@ -429,7 +427,7 @@ __global__ __launch_bounds__(64) void k_small_rad(NepArgs a, const int32_t *__re
         // reverse angular terms, and their half of the per-atom virial
         const int32_t *uA = a.uniA + (size_t)i * a.capA;
         const uint64_t *mA = a.umA + (size_t)i * a.capA;
-        const int32_t *rowA = a.candA + (size_t)i * a.capA;
+        const int32_t *uW = a.uniW + (size_t)i * a.capA;
         const float4 *pbuf = row_at(a.pairbuf + b, i, (uint32_t)a.capA * pstride);
         const int nA = a.uendA[(size_t)i * kMaxSpecies + S - 1];
         float g = 0.0f;
@@ -440,7 +438,7 @@ __global__ __launch_bounds__(64) void k_small_rad(NepArgs a, const int32_t *__re
             if (e < nA && ((mA[e] >> b) & 1u)) {
                 const int slot = uA[e];
                 d = *row_at(pbuf, slot, pstride);
-                if (a.Watom) pair_vec<true>(*row_at(p4b, rowA[slot] >> 2, pstride), pi, lm, dx, dy, dz);
+                if (a.Watom) pair_vec<true>(*row_at(p4b, uW[e] >> 2, pstride), pi, lm, dx, dy, dz);
             }
             float *o = sv + lane * kPad;
             o[0] = d.x; o[1] = d.y; o[2] = d.z;

@@ -679,6 +679,10 @@ __global__ __launch_bounds__(256) void k_candidates(const double *__restrict__ c
 // they took 64 / G serial steps a round).  Per call: 16 water boxes of 192 to
 // 3072 atoms x 32 beads 194 -> 95 us, 4608 water atoms 39 -> 27 us, 4096
 // atoms x 32 beads 20.5 -> 12.6 us, 32000 x 32 116 -> 63 us.
+// Writing the angular entries' words and reverse slots as well takes 10 to
+// 12 us of the two large cases and saves the force kernels a dependent gather
+// per entry: 32000 x 32 with nine radial functions 3145 -> 3043 us in all,
+// the water boxes 1492 -> 1476 us, 16384 x 16 with five 474 -> 456 us.
 constexpr double kShellEps = 1e-3;   // A; far above the rounding of d and s
 constexpr int kRevRows = 4;          // partners' rows whose loads are in flight together
 constexpr int kUnionRounds = 4;      // shell rounds whose partner loads are in flight together
@@ -697,7 +701,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                                                const int32_t *__restrict__ lenR, const int32_t *__restrict__ lenA,
                                                int capR, int capA, int32_t *__restrict__ uniR,
                                                uint64_t *__restrict__ umR, int32_t *__restrict__ uendR,
-                                               int32_t *__restrict__ uniA, uint64_t *__restrict__ umA,
+                                               int32_t *__restrict__ uniA, int32_t *__restrict__ uniW,
+                                               int32_t *__restrict__ uniV, uint64_t *__restrict__ umA,
                                                int32_t *__restrict__ uendA, uint32_t *__restrict__ status,
                                                const uint32_t *__restrict__ grid, const int32_t *__restrict__ types,
                                                int32_t *__restrict__ revA)
@@ -791,6 +796,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const bool kin = k < kend;
             const int32_t wrow = kin ? row[k] : 0;
             const int j = kin ? wrow >> 2 : i;
+            const int rv = kind && kin ? revA[(size_t)i * cap + k] : 0;
             // d + s < rc - eps and d - s > rc + eps, on squares
             bool all_in, out;
             if (FINE) {
@@ -848,9 +854,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const uint64_t bal = __ballot(keep);
             const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
             if (keep) {
-                // radial lists keep the atom index, angular ones the candidate slot
+                // radial lists keep the atom index, angular ones the
+                // candidate slot and beside it what the force kernels look
+                // up by it, so that their gathers wait on one load less
                 uni[cnt + rank] = kind ? k : j;
                 um[cnt + rank] = mask;
+                if (kind) {
+                    uniW[(size_t)i * cap + cnt + rank] = wrow;
+                    uniV[(size_t)i * cap + cnt + rank] = rv;
+                }
             }
             cnt += __popcll(bal);
             for (int t = 0; t < S; ++t) cntS[t] += __popcll(__ballot(keep && (wrow & 3) == t));
@@ -1060,7 +1072,7 @@ extern "C" int32_t neighbor_build_batched(const nep_model *m, nep_nlist *nl, con
                            reinterpret_cast<const float4 *>(nl->cen4), P, N, nl->S, lg, nl->atom_sys, nl->geom, cR, cA,
                            nl->candR, nl->offR, nl->candA, nl->offA, nl->candRs, nl->candAs, nl->lenR, nl->lenA,
                            nl->capR, nl->capA, nl->uniR, nl->umR,
-                           nl->uendR, nl->uniA, nl->umA, nl->uendA, nl->status, nl->grid, types, nl->revA);
+                           nl->uendR, nl->uniA, nl->uniW, nl->uniV, nl->umA, nl->uendA, nl->status, nl->grid, types, nl->revA);
     }
     NEP_HIP(hipGetLastError());
     nl->built = 1;

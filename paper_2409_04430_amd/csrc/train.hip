@@ -246,9 +246,8 @@ void k_train_row(NepArgs a, TrainArgs ta, const float *__restrict__ prm, const i
     }
 
     // ---- angular: per lane one neighbour's basis, harmonics and their derivatives along d
-    const int32_t *uA = a.uniA + (size_t)i * a.capA;
+    const int32_t *uW = a.uniW + (size_t)i * a.capA;
     const uint64_t *mA = a.umA + (size_t)i * a.capA;
-    const int32_t *rowA = a.candA + (size_t)i * a.capA;
     const int nA = uendA[S - 1];
     float f[KA1], fp[KA1], Y[kNumSH], Dm[kNumSH], rdot = 0.0f;
     int tj = 0;
@@ -267,7 +266,7 @@ void k_train_row(NepArgs a, TrainArgs ta, const float *__restrict__ prm, const i
             Dm[m] = 0.0f;
         }
         if (e < nA && ((mA[e] >> b) & 1u)) {
-            const int32_t w = rowA[uA[e]];
+            const int32_t w = uW[e];
             tj = w & 3;
             const float4 dj = *row_at(dFb, w >> 2, pstride);
             float dx, dy, dz, ex, ey, ez;
@@ -812,7 +811,8 @@ extern "C" int32_t nep_param_grad_batched(const nep_model *m, nep_nlist *nl, nep
     a.H = h.hidden; a.P = P; a.lg = lanes_log2(P);
     a.geom = nl->geom; a.tile_atom0 = ws->tile_atom0; a.tile_atom1 = ws->tile_atom1; a.tile_sys = ws->tile_sys;
     a.rcRinv = (float)(1.0 / h.rc_radial); a.rcAinv = (float)(1.0 / h.rc_angular);
-    a.candA = nl->candA; a.revA = nl->revA; a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA;
+    a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA;
+    a.uniW = nl->uniW; a.uniV = nl->uniV;
     a.umR = nl->umR; a.umA = nl->umA; a.uendA = nl->uendA; a.capR = nl->capR; a.capA = nl->capA;
     a.oR = m->off.cR; a.oA = m->off.cA; a.oq = m->off.qs; a.oW0 = m->off.W0; a.ob0 = m->off.b0;
     a.ow1 = m->off.w1; a.ob1 = m->off.b1; a.osh = m->off.sh;
