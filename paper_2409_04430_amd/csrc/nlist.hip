@@ -240,30 +240,36 @@ __device__ void grid_decision(const SysGeom *__restrict__ geom, int nsys, double
                               const float *__restrict__ cmax, int nblk)
 {
     DevGlobal *dg = dev_global(grid);
-    // maxima over the centroid kernel's workgroups
+    // maxima over the centroid kernel's workgroups, and the smallest edge
+    // ratio over the systems (one per thread: walked by every thread, 16
+    // systems took 10 us)
     __shared__ float dred[2][32];
+    __shared__ double lred[32];
     float spread = 0.0f, reach1 = 0.0f;
     for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
         const float2 v = *reinterpret_cast<const float2 *>(cmax + 2 * (size_t)k);
         spread = fmaxf(spread, v.x);
         reach1 = fmaxf(reach1, v.y);
     }
+    double lam_min = 1.0;
+    for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
+        const DevSys *ds = dev_sys(grid, s);
+        for (int a = 0; a < 3; ++a)
+            if (!geom[s].tri && ds->Lb[a] > 0.0) lam_min = fmin(lam_min, geom[s].L[a] / ds->Lb[a]);
+    }
     spread = wave_max_f(spread);
     reach1 = wave_max_f(reach1);
+    for (int o = 32; o > 0; o >>= 1) lam_min = fmin(lam_min, __shfl_xor(lam_min, o));
     if ((threadIdx.x & 63) == 0) {
         dred[0][threadIdx.x >> 6] = spread;
         dred[1][threadIdx.x >> 6] = reach1;
+        lred[threadIdx.x >> 6] = lam_min;
     }
     __syncthreads();
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
         spread = fmaxf(spread, dred[0][w]);
         reach1 = fmaxf(reach1, dred[1][w]);
-    }
-    double lam_min = 1.0;
-    for (int s = 0; s < nsys; ++s) {
-        const DevSys *ds = dev_sys(grid, s);
-        for (int a = 0; a < 3; ++a)
-            if (!geom[s].tri && ds->Lb[a] > 0.0) lam_min = fmin(lam_min, geom[s].L[a] / ds->Lb[a]);
+        lam_min = fmin(lam_min, lred[w]);
     }
     const double reach = 2.0 * (double)reach1, d0 = 2.0 * (double)dg->d_build;
     const double needR = (rcR + reach) / lam_min - rcR - d0, needA = (rcA + reach) / lam_min - rcA - d0;
@@ -289,16 +295,16 @@ __device__ void grid_decision(const SysGeom *__restrict__ geom, int nsys, double
         }
     }
     __syncthreads();   // every thread has read the record of the last rebuild
+    // general cells: centroid distances are nearest-image distances only
+    // below the smallest face distance (mic_vec), and every candidate
+    // pair must lie there (rows of radius R_rows)
+    for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
+        if (!geom[s].tri) continue;
+        const double wmin = fmin(geom[s].w[0], fmin(geom[s].w[1], geom[s].w[2]));
+        if (!(R_rows < wmin)) atomicOr(&status[0], (uint32_t)NEP_FLAG_CELL_TOO_SMALL);
+    }
     if (threadIdx.x == 0) {
         dg->rebuild = rebuild;
-        // general cells: centroid distances are nearest-image distances only
-        // below the smallest face distance (mic_vec), and every candidate
-        // pair must lie there (rows of radius R_rows)
-        for (int s = 0; s < nsys; ++s) {
-            if (!geom[s].tri) continue;
-            const double wmin = fmin(geom[s].w[0], fmin(geom[s].w[1], geom[s].w[2]));
-            if (!(R_rows < wmin)) atomicOr(&status[0], (uint32_t)NEP_FLAG_CELL_TOO_SMALL);
-        }
         atomicMax(&status[4], __float_as_uint(spread));
         if (!rebuild) {
             // reused rows that were truncated keep the overflow flag raised
