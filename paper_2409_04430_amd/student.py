@@ -322,14 +322,23 @@ class StudentPimd:
         e = self.eng
         self.tws.compute(e.nl, e.pos, e.box, e.types, E, F, W)
 
-    def forces(self, judge: bool = True):
+    def _judged(self) -> bool:
+        """Whether this step's student forces are judged."""
+        return bool(self.on_student and self.judge_every and self.eng.step_no % self.judge_every == 0)
+
+    def forces(self, judge: bool = True, defer: bool = False):
+        """defer: E and W are completed by the next `pimd.step_nep` with the
+        workspace that computed them (not at a judged step)."""
         e = self.eng
+        judge = judge and self._judged()
         e.nl.build(e.pos, e.box, e.types)
+        if defer and not judge:
+            (e.ws if self.on_student else self.tws).defer_reduce()
         if not self.on_student:
             self._teacher(e.E, e.F, e.W)
             return
         e.ws.compute(e.nl, e.pos, e.box, e.types, e.E, e.F, e.W)
-        if judge and self.judge_every and e.step_no % self.judge_every == 0:
+        if judge:
             self._teacher(self.Et, self.Ft, self.Wt)
             r = float(lib.force_rmse(e.F, self.Ft, self.work))
             self.history.append((e.step_no, r))
@@ -358,8 +367,12 @@ class StudentPimd:
         e = self.eng
         if not e.started:
             self.start()
-        self.forces()
-        e.pimd.step(e.pos, e.vel, e.F, e.step_no, lib.FUSED)
+        if self._judged():
+            self.forces()
+            e.pimd.step(e.pos, e.vel, e.F, e.step_no, lib.FUSED)
+        else:   # the E/W sums ride in the integrator launch
+            self.forces(defer=True)
+            e.pimd.step_nep(e.pos, e.vel, e.F, e.step_no, lib.FUSED, e.ws if self.on_student else self.tws)
         e.step_no += 1
 
     def step(self):
