@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     double Wo[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) Wo[c] = Wv[comp[c]];
-    bead_block_sums(Wo, ok, lds, P, a.lg, a.partW1 + blockIdx.x, nblk, 9 * nblk);
+    bead_block_sums(Wo, ok, lds, P, a.lg, a.partW1 + blockIdx.x, nblk, 9 * nblk, blockDim.x >> 6);
 }
 
 // One workgroup per (bead, component c): c = 0 energy, 1..9 virial; partial

@@ -41,7 +41,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
     // b0 [S][H], w1 [S][H]
     extern __shared__ float dyn[];
     constexpr int D = Dims<NR1, NA1, FOUR>::D;
-    const LaneMap lm = lane_map(a);
+    const LaneMap lm = lane_map(a, threadIdx.x);
     const int i = lm.i, b = lm.b, P = a.P, S = a.S;
     const bool valid = lm.valid;
     const int ti = a.types[i];
@@ -82,7 +82,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
         for (int v = 0; v < D; ++v) q[v] = 0.0f;
         // the wavefront's adjoint rows, interleaved (adj_rows): each float4
         // store or load of the wavefront covers 1 KiB contiguously
-        const __amdgpu_buffer_rsrc_t Bo = adj_rows(a.B, NA1 * (kNumSH / 4));
+        const __amdgpu_buffer_rsrc_t Bo = adj_rows(a.B, NA1 * (kNumSH / 4), threadIdx.x, blockDim.x);
         // A stays in registers through the network for small angular sets;
         // otherwise it is parked in the lane's adjoint row, where the
         // angular force kernel reads it
@@ -348,7 +348,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
         // angular force kernel from them and the descriptor adjoints stored
         // here (no read-back of the parked sums)
         if constexpr (PARK) {
-            const __amdgpu_buffer_rsrc_t go = adj_rows(a.Gad, gad_q(NA1, FOUR));
+            const __amdgpu_buffer_rsrc_t go = adj_rows(a.Gad, gad_q(NA1, FOUR), threadIdx.x, blockDim.x);
 #pragma unroll
             for (int n = 0; n < NA1; ++n)
                 adj_store(go, n, make_float4(G[NR1 + n], G[NR1 + NA1 + n], G[NR1 + 2 * NA1 + n], G[NR1 + 3 * NA1 + n]));
@@ -405,7 +405,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
     __shared__ SumLds<1> lds;
     // partials bead-major, [P][workgroups]: the reduction reads them contiguously
     const float Us[1] = {U};
-    bead_block_sums(Us, valid, lds, P, a.lg, a.partE + blockIdx.x, 0, gridDim.x);
+    bead_block_sums(Us, valid, lds, P, a.lg, a.partE + blockIdx.x, 0, gridDim.x, blockDim.x >> 6);
 }
 
 // ------------------------------------------------ pass 2: angular, own ---
@@ -424,16 +424,33 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
 // past their atom's last candidate or outside the cutoff compute on a dummy
 // pair and contribute nothing; a candidate outside for every lane is
 // skipped.
-constexpr int kBatchAng = 4;   // angular entries whose loads are issued together
+// How a row's own angular sums are taken: over the whole list, in two parts
+// one after the other (systems of up to kTwoPartRows rows among the launch's),
+// or in two parts by two lanes, in launches of up to kSplitWaves wavefronts,
+// which leave each SIMD's place for a second one empty (all their systems are
+// that small).  2048 atoms x 32 beads with five functions, whole call: 172 us
+// by one lane, 161 by two; training on 8 x 256 atoms x 32, 606 and 596.  At
+// twice the rows two lanes cost more than they give, the adjoint rows being
+// read twice: 4096 x 32, 214 and 255 us.  In two parts by one lane the water
+// boxes take 1478 us, as a whole 1470.
+constexpr int kSumWhole = 0, kSumParts = 1, kSumLanes = 2;
+constexpr int kSplitWaves = kTwoPartRows / 64;
+
 // Wavefronts per SIMD of k_force_ang.
 template <int NA1> constexpr int kAngWaves() { return NA1 > 5 ? 1 : 2; }
 constexpr int kBatchRev = 8;   // reverse angular terms read together by the radial force kernel
 
-template <int NA1, int KA1, bool FOUR, bool PARKED, bool FINE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAngWaves<NA1>())))
+template <int NA1, int KA1, bool FOUR, bool PARKED, bool FINE, int SUM>
+__global__ __launch_bounds__(SUM == kSumLanes ? 2 * kBlock : kBlock) __attribute__((amdgpu_waves_per_eu(kAngWaves<NA1>())))
 void k_force_ang(NepArgs a, const float *__restrict__ prm)
 {
-    const LaneMap lm = lane_map(a);
+    // this lane's row (thread of the descriptor's workgroup), and the part of
+    // the list it takes with two lanes per row
+    constexpr bool SPLIT = SUM == kSumLanes;
+    const int thread = SPLIT ? (threadIdx.x >> 6) * 32 + (threadIdx.x & 31) : threadIdx.x;
+    const int threads = SPLIT ? blockDim.x >> 1 : blockDim.x;
+    const int part = SPLIT ? (threadIdx.x >> 5) & 1 : 0;
+    const LaneMap lm = lane_map(a, thread);
     const int i = lm.i, b = lm.b, P = a.P, S = a.S;
     const bool valid = lm.valid;
     const int ti = a.types[i];
@@ -450,6 +467,15 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
     float Wv[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) Wv[e] = 0.0f;
+    __shared__ float first[SUM ? 12 : 1][SUM ? kBlock : 1];   // the first part's sums of each row
+    bool parts = SPLIT;
+    if constexpr (SUM == kSumParts) {
+        const int sy = a.tile_sys[blockIdx.x];
+        const int n = a.tile_atom1[a.sys_tile0[sy + 1] - 1] - a.tile_atom0[a.sys_tile0[sy]];
+        parts = (int64_t)n * P <= kTwoPartRows;
+    }
+    __shared__ SumLds<9> lds;
+    bool second = false;   // in the second part
 
     uint64_t todo = __ballot(valid && tok);
     while (todo) {
@@ -465,25 +491,25 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
         float Bi[NA1][kNumSH];
         bool formed = false;   // wave-uniform
         auto get_adjoints = [&]() {
-            const __amdgpu_buffer_rsrc_t bi4 = adj_rows(a.B, NA1 * (kNumSH / 4));
+            const __amdgpu_buffer_rsrc_t bi4 = adj_rows(a.B, NA1 * (kNumSH / 4), thread, threads);
 #pragma unroll
             for (int n = 0; n < NA1; ++n)
 #pragma unroll
                 for (int q4 = 0; q4 < kNumSH / 4; ++q4) {
-                    const float4 v4 = adj_load(bi4, n * (kNumSH / 4) + q4);
+                    const float4 v4 = adj_load(bi4, n * (kNumSH / 4) + q4, thread);
                     Bi[n][4 * q4] = v4.x; Bi[n][4 * q4 + 1] = v4.y;
                     Bi[n][4 * q4 + 2] = v4.z; Bi[n][4 * q4 + 3] = v4.w;
                 }
             if constexpr (PARKED) {
-                const __amdgpu_buffer_rsrc_t gi = adj_rows(a.Gad, gad_q(NA1, FOUR));
+                const __amdgpu_buffer_rsrc_t gi = adj_rows(a.Gad, gad_q(NA1, FOUR), thread, threads);
                 const float *shc = prm + a.osh;
 #pragma unroll
                 for (int n = 0; n < NA1; ++n) {
-                    const float4 gl = adj_load(gi, n);
+                    const float4 gl = adj_load(gi, n, thread);
                     const float Gl[kLmax] = {gl.x, gl.y, gl.z, gl.w};
                     float g4 = 0.0f;
                     if constexpr (FOUR) {
-                        const float4 q = adj_load(gi, NA1 + n / 4);
+                        const float4 q = adj_load(gi, NA1 + n / 4, thread);
                         g4 = (n & 3) == 0 ? q.x : (n & 3) == 1 ? q.y : (n & 3) == 2 ? q.z : q.w;
                     }
                     form_adjoint<FOUR>(Bi[n], Gl, g4, shc, Bi[n]);
@@ -492,9 +518,21 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
             formed = true;
         };
         for (int t = 0; t < S; ++t) {
-            int s0 = 0, s1 = 0;
-            if (mine) block_range(a.uendA, i, t, s0, s1);
-            const int cnt = s1 - s0;
+            int s0 = 0, s1 = 0, hp = 0;
+            if (mine) {
+                block_range(a.uendA, i, t, s0, s1);
+                if (SUM) hp = half_point(a.uendA[(size_t)i * kMaxSpecies + S - 1]);
+            }
+            int cnt = s1 - s0;
+            // where the second part begins in this block (-1: not here)
+            int mid = -1;
+            if constexpr (SUM != kSumWhole) mid = split_batches(s0, s1, hp) * kBatchAng;
+            if constexpr (SPLIT) {   // this lane's part of the block
+                s0 += part ? mid : 0;
+                cnt = part ? cnt - mid : min(cnt, mid);
+            } else if (!parts || second || mid >= cnt) {
+                mid = -1;
+            }
             int cmax = cnt;
             for (int o = 32; o > 0; o >>= 1) cmax = max(cmax, __shfl_xor(cmax, o));
             cmax = __builtin_amdgcn_readfirstlane(cmax);
@@ -514,6 +552,20 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                 for (int u = 0; u < kBatchAng; ++u) aq[u] = (sb + u < cnt) & ((mm.v[u] & bit) != 0);
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) pq[u] = *row_at(p4b, jq.v[u] >> 2, pstride);
+                if constexpr (SUM == kSumParts) {
+                    if (sb == mid) {   // the first part ends here
+                        second = true;
+                        first[0][threadIdx.x] = Fx;
+                        first[1][threadIdx.x] = Fy;
+                        first[2][threadIdx.x] = Fz;
+                        Fx = Fy = Fz = 0.0f;
+#pragma unroll
+                        for (int e = 0; e < 9; ++e) {
+                            first[3 + e][threadIdx.x] = Wv[e];
+                            Wv[e] = 0.0f;
+                        }
+                    }
+                }
                 if (!formed) get_adjoints();
 #pragma unroll
                 for (int u = 0; u < kBatchAng; ++u) keep(pq[u]);
@@ -573,7 +625,21 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
         }
     }
 
-    if (valid) {
+    // the two parts together
+    if constexpr (SPLIT) {
+        Fx += __shfl_xor(Fx, 32);
+        Fy += __shfl_xor(Fy, 32);
+        Fz += __shfl_xor(Fz, 32);
+#pragma unroll
+        for (int e = 0; e < 9; ++e) Wv[e] += __shfl_xor(Wv[e], 32);
+    } else if (SUM == kSumParts && second) {
+        Fx += first[0][threadIdx.x];
+        Fy += first[1][threadIdx.x];
+        Fz += first[2][threadIdx.x];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) Wv[e] += first[3 + e][threadIdx.x];
+    }
+    if (valid && part == 0) {
         float *Fo = a.Fang + ((size_t)i * P + b) * 3;
         Fo[0] = Fx;
         Fo[1] = Fy;
@@ -585,8 +651,18 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
             for (int e = 0; e < 9; ++e) wo[e] = 0.5f * Wv[e];
         }
     }
-    __shared__ SumLds<9> lds;
-    bead_block_sums(Wv, valid, lds, P, a.lg, a.partWa + blockIdx.x, gridDim.x, 9 * gridDim.x);
+    bool sum = valid;
+    if constexpr (SPLIT) {   // back to the rows' own threads for the sums over atoms
+        if (part == 0) {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) first[e][thread] = valid ? Wv[e] : 0.0f;
+        }
+        __syncthreads();
+        sum = (int)threadIdx.x < threads;
+#pragma unroll
+        for (int e = 0; e < 9; ++e) Wv[e] = first[e][sum ? threadIdx.x : 0];
+    }
+    bead_block_sums(Wv, sum, lds, P, a.lg, a.partWa + blockIdx.x, gridDim.x, 9 * gridDim.x, threads >> 6);
 }
 
 // ----------------------------------------- pass 3: radial + combination ---
@@ -599,7 +675,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
 template <int KR1, bool FINE>
 __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
 {
-    const LaneMap lm = lane_map(a);
+    const LaneMap lm = lane_map(a, threadIdx.x);
     const int i = lm.i, b = lm.b, P = a.P, S = a.S;
     const bool valid = lm.valid;
     const int ti = a.types[i];
@@ -736,7 +812,7 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
         if (!(isfinite(gx) && isfinite(gy) && isfinite(gz))) atomicOr(a.flags, (uint32_t)NEP_FLAG_NONFINITE);
     }
     __shared__ SumLds<9> lds;
-    bead_block_sums(Wf, valid, lds, P, a.lg, a.partWr + blockIdx.x, gridDim.x, 9 * gridDim.x);
+    bead_block_sums(Wf, valid, lds, P, a.lg, a.partWr + blockIdx.x, gridDim.x, 9 * gridDim.x, blockDim.x >> 6);
 }
 
 // Per-(system, bead) energy and virial from the per-workgroup partial sums
@@ -752,7 +828,8 @@ constexpr size_t kNetLdsMax = 60 * 1024;   // bytes of LDS for the staged networ
 
 // mlp: NEP_MLP_FP32 (vector units), NEP_MLP_BF16_MFMA or NEP_MLP_FP32_MFMA (matrix cores).
 template <int NR1, int NA1, bool FOUR, bool FINE>
-static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int mlp, bool lds_net, hipStream_t s)
+static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int64_t min_rows, int mlp,
+                     bool lds_net, hipStream_t s)
 {
     const dim3 g(nblk);
     const dim3 blk(64 * wpb);
@@ -773,12 +850,20 @@ static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int 
     {
         ProfScope ps_(K_FORCE_ANG, s);
         const bool parked = adj_parked(mlp == NEP_MLP_BF16_MFMA || mlp == NEP_MLP_FP32_MFMA, NA1);
-        if constexpr (adj_parked(false, NA1))   // wide sets are always parked
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE>), g, blk, 0, s, a, prm);
-        else if (parked)
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE>), g, blk, 0, s, a, prm);
-        else
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE>), g, blk, 0, s, a, prm);
+        if constexpr (adj_parked(false, NA1)) {   // wide sets are always parked
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumWhole>), g, blk, 0, s, a, prm);
+        } else if (two_parts(NA1, a.lg) && nblk * wpb <= kSplitWaves) {
+            const dim3 b2(128 * wpb);
+            if (parked) hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumLanes>), g, b2, 0, s, a, prm);
+            else hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE, kSumLanes>), g, b2, 0, s, a, prm);
+        } else if (two_parts(NA1, a.lg) && min_rows <= kTwoPartRows) {
+            if (parked) hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumParts>), g, blk, 0, s, a, prm);
+            else hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE, kSumParts>), g, blk, 0, s, a, prm);
+        } else if (parked) {
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumWhole>), g, blk, 0, s, a, prm);
+        } else {
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE, kSumWhole>), g, blk, 0, s, a, prm);
+        }
     }
     {
         ProfScope ps_(K_FORCE, s);
@@ -788,11 +873,11 @@ static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int 
 
 // Lists with fixed-point positions and lists with fine-grid positions (general cells, long edges).
 template <int NR1, int NA1, bool FOUR>
-static void launch(const NepArgs &a, const float *prm, int nblk, int wpb, bool fine, int mlp, bool lds_net,
-                   hipStream_t s)
+static void launch(const NepArgs &a, const float *prm, int nblk, int wpb, int64_t min_rows, bool fine, int mlp,
+                   bool lds_net, hipStream_t s)
 {
-    if (fine) launch_t<NR1, NA1, FOUR, true>(a, prm, nblk, wpb, mlp, lds_net, s);
-    else launch_t<NR1, NA1, FOUR, false>(a, prm, nblk, wpb, mlp, lds_net, s);
+    if (fine) launch_t<NR1, NA1, FOUR, true>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
+    else launch_t<NR1, NA1, FOUR, false>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
 }
 
 }  // namespace nep
@@ -836,7 +921,7 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     // packed positions of the last neighbor_build (the same positions, see the header)
     a.p4 = reinterpret_cast<const float4 *>(nl->pos4); a.pos = pos; a.types = types; a.N = N; a.S = h.n_species;
     a.H = h.hidden; a.P = P; a.lg = lanes_log2(P);
-    a.geom = nl->geom; a.tile_atom0 = ws->tile_atom0; a.tile_atom1 = ws->tile_atom1; a.tile_sys = ws->tile_sys;
+    a.geom = nl->geom; a.tile_atom0 = ws->tile_atom0; a.tile_atom1 = ws->tile_atom1; a.tile_sys = ws->tile_sys; a.sys_tile0 = ws->sys_tile0;
     a.rcRinv = (float)(1.0 / h.rc_radial); a.rcAinv = (float)(1.0 / h.rc_angular);
     a.kappa4 = (float)(-4.5 * std::sqrt(2.0 / 35.0) * std::pow(5.0 / (4.0 * M_PI), 1.5));
     a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA;
@@ -862,12 +947,15 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     } else {
         const int key = h.n_max_radial * 100 + h.n_max_angular * 10 + h.four_body;
         const bool fine = nl->fine_pos != 0;
+        int64_t min_rows = INT64_MAX;   // the smallest (non-empty) system
+        for (int sy = 0; sy < nsys; ++sy)
+            if (ws->off[sy + 1] > ws->off[sy]) min_rows = std::min(min_rows, (int64_t)P * (ws->off[sy + 1] - ws->off[sy]));
         switch (key) {
-        case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-        case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-        case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-        case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
-        case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, fine, mlp, !ws->net_global, s); break;
+        case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
+        case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
+        case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
+        case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
+        case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
         default: return fail(NEP_ERR_UNSUPPORTED, "nep_compute: unsupported model shape");
         }
         r.partE = ws->partE; r.partWa = a.partWa; r.partWr = a.partWr;

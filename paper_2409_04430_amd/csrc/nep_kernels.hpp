@@ -17,6 +17,7 @@ struct NepArgs {
     int N, S, H, P, lg;  // lg: log2 of the lanes per atom
     const SysGeom *geom; // per system: fine grid of the packed positions
     const int32_t *tile_atom0, *tile_atom1, *tile_sys;   // per workgroup: atom range and system
+    const int32_t *sys_tile0;    // per system: its first workgroup
     float rcRinv, rcAinv;
     float kappa4;
     // union lists of the neighbour handle
@@ -41,7 +42,7 @@ struct NepArgs {
     const uint16_t *w0b; // BF16 first-layer weights of the matrix-core network ([S][2][32][32])
 };
 
-// Lane -> (atom, bead): the beads of one atom occupy 2^lg adjacent lanes;
+// Thread of the workgroup -> (atom, bead): the beads of one atom occupy 2^lg adjacent lanes;
 // a workgroup takes one tile (an atom range of one system).  M and h are
 // the fine grid of the tile's system (wave-uniform).
 struct LaneMap {
@@ -53,11 +54,11 @@ struct LaneMap {
     int form;        // PosForm of the tile's system
     float hv[9];
 };
-__device__ __forceinline__ LaneMap lane_map(const NepArgs &a)
+__device__ __forceinline__ LaneMap lane_map(const NepArgs &a, int thread)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = thread & 63;
     const int a0 = a.tile_atom0[blockIdx.x], a1 = a.tile_atom1[blockIdx.x];
-    const int ia = a0 + (threadIdx.x >> 6) * (64 >> a.lg) + (lane >> a.lg);
+    const int ia = a0 + (thread >> 6) * (64 >> a.lg) + (lane >> a.lg);
     const int b = lane & ((1 << a.lg) - 1);
     LaneMap m;
     m.valid = ia < a1 && b < a.P;
@@ -98,6 +99,24 @@ __device__ __forceinline__ LaneMap row_map(const SysGeom &g, int i, int b)
     return m;
 }
 
+// The own angular sums of a row (force and virial) of a system of up to
+// kTwoPartRows rows are taken in two parts, the second from the first batch
+// of kBatchAng entries (batches start at each species block) that begins at
+// or past half of the list: launches too small to fill the chip give the
+// parts to different lanes, and the system keeps its bits in a larger batch.
+// half_point is that half, split_batches the number of batches of block
+// [s0, s1) in the first part.  Only where a second wavefront fits a SIMD (up
+// to five radial functions) and both parts of a row a wavefront (two_parts).
+constexpr int kTwoPartRows = 65536;   // 64 lanes on each SIMD of 256 compute units
+constexpr bool two_parts(int NA1, int lg) { return NA1 <= 5 && lg <= 5; }
+constexpr int kBatchAng = 4;   // angular entries whose loads are issued together
+__device__ __forceinline__ int half_point(int n) { return (n + 1) >> 1; }
+__device__ __forceinline__ int split_batches(int s0, int s1, int hp)
+{
+    const int nb = (s1 - s0 + kBatchAng - 1) / kBatchAng;
+    return min(max((hp - s0 + kBatchAng - 1) / kBatchAng, 0), nb);
+}
+
 // Start and end of species block t in a union list.
 __device__ __forceinline__ void block_range(const int32_t *uend, int i, int t, int &s0, int &s1)
 {
@@ -126,7 +145,8 @@ __device__ __forceinline__ double wave_sum(double v)
 // Per-bead sums of NV values over the atoms of a block, in a fixed order:
 // each wavefront's atoms (adjacent groups of 2^lg lanes) pairwise by a
 // butterfly, the wavefronts then one after another; out[e * vstride +
-// b * stride] for value e and bead b < P.  kSumVals values share one barrier
+// b * stride] for value e and bead b < P, over the block's first nw
+// wavefronts.  kSumVals values share one barrier
 // pair; the butterflies replace a serial walk over the block's atoms by one
 // lane per bead (256 / 2^lg dependent LDS reads per value).  reduce_output
 // takes the same order from per-row values.
@@ -135,9 +155,9 @@ template <int NV>
 struct SumLds { double v[(NV < kSumVals ? NV : kSumVals) * kBlock]; };
 template <int NV, typename T>
 __device__ __forceinline__ void bead_block_sums(const T (&v)[NV], bool valid, SumLds<NV> &lds, int P, int lg,
-                                                double *out, size_t vstride, int stride)
+                                                double *out, size_t vstride, int stride, int nw)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6, G = 1 << lg;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, G = 1 << lg;
     constexpr int NS = NV < kSumVals ? NV : kSumVals;
 #pragma unroll
     for (int e0 = 0; e0 < NV; e0 += NS) {
@@ -146,10 +166,10 @@ __device__ __forceinline__ void bead_block_sums(const T (&v)[NV], bool valid, Su
         for (int x = 0; x < NS; ++x) {
             double s = valid ? (double)v[e0 + x < NV ? e0 + x : NV - 1] : 0.0;
             for (int o = 32; o >= G; o >>= 1) s += __shfl_xor(s, o);
-            if (lane < G) lds.v[(x * nw + wv) * G + lane] = s;
+            if (lane < G && wv < nw) lds.v[(x * nw + wv) * G + lane] = s;
         }
         __syncthreads();
-        for (int x = wv; x < NS; x += nw) {
+        for (int x = wv; x < NS; x += blockDim.x >> 6) {
             if (lane < P && e0 + x < NV) {
                 double s = 0.0;
                 for (int w = 0; w < nw; ++w) s += lds.v[(x * nw + w) * G + lane];
@@ -175,10 +195,11 @@ __device__ __forceinline__ void bead_block_sums(const T (&v)[NV], bool valid, Su
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kBufWord3 = 0x00020000;   // buffer resource word 3 of gfx9-family chips: 32-bit data format
 
-// nq: float4 entries per lane.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t adj_rows(float *B, int nq)
+// nq: float4 entries per lane; thread and threads: the lane's place in the
+// descriptor's workgroup and its size.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t adj_rows(float *B, int nq, int thread, int threads)
 {
-    const uint32_t w = __builtin_amdgcn_readfirstlane((uint32_t)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    const uint32_t w = __builtin_amdgcn_readfirstlane((uint32_t)(blockIdx.x * (threads >> 6) + (thread >> 6)));
     const int bytes = nq * 64 * 16;
     return __builtin_amdgcn_make_buffer_rsrc(B + (size_t)w * (bytes / 4), (short)0, bytes, kBufWord3);
 }
@@ -208,9 +229,9 @@ __device__ __forceinline__ void adj_store(__amdgpu_buffer_rsrc_t r, int q, float
     __builtin_amdgcn_raw_buffer_store_b128(u, r, o + q * 1024, 0, 0);
 }
 
-__device__ __forceinline__ float4 adj_load(__amdgpu_buffer_rsrc_t r, int q)
+__device__ __forceinline__ float4 adj_load(__amdgpu_buffer_rsrc_t r, int q, int thread)
 {
-    const u32x4_t u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(threadIdx.x & 63) * 16, q * 1024, 0);
+    const u32x4_t u = __builtin_amdgcn_raw_buffer_load_b128(r, (thread & 63) * 16, q * 1024, 0);
     return make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w));
 }
 

@@ -289,7 +289,17 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
     const int32_t *uV = a.uniV + (size_t)i * a.capA;
     float4 *pairb = a.pairbuf + b;
     const int we = lane - 3, wa = we / 3, wb = we - 3 * wa;
-    float acc = 0.0f;
+    float acc = 0.0f, first = 0.0f;
+    // entry where the second part of the sums begins (half_point)
+    int mid = nA;
+    if (two_parts(NA1, a.lg)) {
+        const int hp = half_point(nA);
+        for (int t = S - 1; t >= 0; --t) {
+            const int s0 = t ? uendA[t - 1] : 0, s1 = uendA[t];
+            const int m = s0 + split_batches(s0, s1, hp) * kBatchAng;
+            if (m < s1) mid = m;
+        }
+    }
     for (int p0 = 0; p0 < nA; p0 += 64) {
         const int e = p0 + lane;
         const bool act = e < nA && ((mA[e < nA ? e : 0] >> b) & 1u);
@@ -331,16 +341,24 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
         o[0] = px; o[1] = py; o[2] = pz;
         o[3] = dx; o[4] = dy; o[5] = dz;
         wave_lds_sync();
-        const int hi = min(nA - p0, 64);
-        if (lane < 3) {
+        const int hi = min(nA - p0, 64), xm = min(max(mid - p0, 0), hi);
+        for (int h = 0; h < 2; ++h) {
+            const int x0 = h ? xm : 0, x1 = h ? hi : xm;
+            if (h && mid >= p0 && mid < p0 + 64) {
+                first = acc;
+                acc = 0.0f;
+            }
+            if (lane < 3) {
 #pragma unroll 4
-            for (int x = 0; x < hi; ++x) acc += sy[x * kYPad + lane];
-        } else if (lane < 12) {
+                for (int x = x0; x < x1; ++x) acc += sy[x * kYPad + lane];
+            } else if (lane < 12) {
 #pragma unroll 4
-            for (int x = 0; x < hi; ++x) acc = fmaf(-sy[x * kYPad + 3 + wa], sy[x * kYPad + wb], acc);
+                for (int x = x0; x < x1; ++x) acc = fmaf(-sy[x * kYPad + 3 + wa], sy[x * kYPad + wb], acc);
+            }
         }
         wave_lds_sync();
     }
+    acc += first;
     if (lane < 3) {
         a.Fang[((size_t)i * P + b) * 3 + lane] = acc;
     } else if (lane < 12) {
