@@ -144,11 +144,14 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
         }
 
         // angular: A_nlm = sum_j g_n(r_ij) Y_lm(u_ij), NG radial functions n
-        // per pass over the neighbours (all of them when A stays in
-        // registers; in three passes when more than five are parked, so that
-        // the accumulators of one pass fit the registers), each pass's q
-        // entries formed and its A parked before the next
-        constexpr int NG = NA1 > 5 ? (NA1 + 2) / 3 : NA1;
+        // per pass over the neighbours: all of them up to five; in two
+        // passes when more are parked, each pass's q entries formed (keep:
+        // formed later, they would hold the pass's A in scratch) and its A
+        // parked before the next.  32000 atoms x 32 with nine functions:
+        // 1107 us with three passes and 120 spilled registers, 982 without
+        // the spills, 905 with two passes (120 sums, as many as five
+        // functions keep); 13824 x 64 with seven, 461 -> 452 us.
+        constexpr int NG = NA1 > 5 ? (NA1 + 1) / 2 : NA1;
         const int32_t *uW = a.uniW + (size_t)i * a.capA;
         const uint64_t *mA = a.umA + (size_t)i * a.capA;
 #pragma unroll
@@ -229,9 +232,11 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                 for (int m = 0; m < kNumSH; ++m)
                     if (sh_l(m) == l) s2 = fmaf(A[g][m], A[g][m], s2);
                 q[NR1 + (l - 1) * NA1 + n] = s2;
+                if constexpr (PARK) keep(q[NR1 + (l - 1) * NA1 + n]);
             }
             if (FOUR) {
                 q[NR1 + kLmax * NA1 + n] = a.kappa4 * four_body_tr3(&A[g][3], shc);
+                if constexpr (PARK) keep(q[NR1 + kLmax * NA1 + n]);
             }
             if constexpr (PARK) {
                 // park A in this lane's adjoint row (the angular force kernel forms B from it)

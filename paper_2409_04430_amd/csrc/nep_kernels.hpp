@@ -269,6 +269,10 @@ __device__ __forceinline__ void keep(float4 &v)
     asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
 }
 
+// The same for a value whose computation must not be moved past this point
+// (its operands would stay live, or be spilled, until then).
+__device__ __forceinline__ void keep(float &v) { asm volatile("" : "+v"(v)); }
+
 // Model coefficients (read-only during a launch) through the constant
 // address space: loads at a wave-uniform address become scalar loads, which
 // do not wait on the vector gathers in flight.
