@@ -1,7 +1,8 @@
 // NEP energy, forces and virial on gfx950 (site-energy model of Sec. II.C,
 // bead forces and virial of Sec. II.A of arXiv:2409.04430).
 //
-// Four kernels per call, one lane per (bead, atom), neighbours taken from
+// Four kernels per call, one lane per (bead, atom) (small systems: the
+// kernels of nep_small.hip), neighbours taken from
 // the per-bead compact lists built over the shared centroid candidate rows:
 //   k_descriptor  radial sums, angular sums A_nlm = sum_j g_n(r_ij) Y_lm(u_ij)
 //                 over real orthonormal spherical harmonics, q_nl = sum_m A_nlm^2
