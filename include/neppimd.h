@@ -330,9 +330,9 @@ void nep_ws_destroy(nep_ws *ws);
  *   W_atom [P][N][9] dev float32 per-atom virial -1/2 sum_j r_ij (x)
  *                   (dU_i/dr_ij - dU_j/dr_ji), or NULL
  * Positions enter as FP64 and are packed per bead in fixed point
- * (orthorhombic edges up to 256 A) or as fine-grid cell indices plus FP32
- * offsets, from which pair vectors are formed (error about 1e-6 A); the rest is FP32 arithmetic with FP64 accumulation of
- * forces, energies and virials.
+ * (orthorhombic edges up to 200 A) or as fine-grid cell indices plus FP32
+ * offsets, from which pair vectors are formed (error below 1e-6 A); the rest
+ * is FP32 arithmetic with FP64 accumulation of forces, energies and virials.
  * The summation order is fixed, so repeated calls give identical bits.
  * Errors: NEP_ERR_INVALID_ARG (sizes differ from the handles', lists built
  * with other cutoffs than the model's), NEP_ERR_HIP.

@@ -91,7 +91,7 @@ struct SysGeom {
     double L[3], invL[3];     // orthorhombic box edges (triclinic: the diagonal of H, unused)
     double hd[3], Minv[3];    // fine grid spacing and M / L (packing, orthorhombic)
     float h[3];               // fine grid spacing (FP32, pair vectors, orthorhombic)
-    float fx[6];              // L / 2^32, the quantum of fixed-point positions, as two FP32 terms: high [3], low [3]
+    double fx[3];             // L / 2^32, the quantum of fixed-point positions
     int form;                 // packed positions of this system: kPosFixed, kPosGrid or kPosGridTri
     int M[3];                 // fine grid cells per axis (along the cell's edge vectors)
     int nc_cap[3];            // cell-list allocation bound per axis
@@ -378,15 +378,23 @@ FineGrid fine_grid_cell(const CellInfo &c, double rc);
 
 // Fixed-point positions (kPosFixed): per axis the fractional coordinate as a 32-bit
 // integer, so that the wrapped integer difference of two atoms is their
-// minimum image and a pair vector costs 12 instructions (subtraction,
-// conversion, product and its correction per axis) against 24 for the fine
-// grid below, of about 70 per pair in the descriptor's radial loop.  The
-// quantum enters as two FP32 terms: rounded to one, all distances along an
-// axis would carry the same relative error (up to 6e-8, a strain), which
-// the virial of a near-equilibrium crystal magnifies.  The quantum L / 2^32
-// is at most 6e-8 A at the largest edge, the FP32 rounding of the fine
-// grid's offsets; longer edges and general cells keep the fine grid.
-constexpr double kFixedMaxEdge = 256.0;
+// minimum image and a pair vector costs 12 instructions (per axis a
+// subtraction, two conversions and an FP64 product, which runs at the FP32
+// rate) against 24 for the fine grid below, of about 70 per pair in the
+// descriptor's radial loop.  The product of the exact difference and the
+// FP64 quantum L / 2^32 is rounded once, to FP32: the difference rounded to
+// FP32 first and multiplied there had a third more rms error than the fine
+// grid (pairs within 6 A at a 33.6 A edge: 1.29e-7 A, the fine grid 0.94e-7,
+// this form 0.90e-7), and the quantum rounded to FP32 would be a strain,
+// which the virial of a near-equilibrium crystal magnifies.  The whole force
+// call: 4096 x 32 binary atoms 216 us (the FP32 product 213, the difference
+// split into two exact FP32 parts 219), 16 water boxes 1477 (1467, 1490),
+// training on 8 x 256 x 32 578 (594, 598).
+// The quantum's own error grows with the edge; pairs within 4, 5, 6, 8 A
+// have rms errors at 200 A of 5.5, 8.0, 9.2, 10.6e-8 A (fine grid 5.9, 8.2,
+// 9.4, 10.8e-8), at 256 A of 6.1, 8.4, 9.6, 10.9e-8.  Longer edges than the
+// bound and general cells keep the fine grid.
+constexpr double kFixedMaxEdge = 200.0;
 
 // Fixed-point form of one position: integers in x, y, z, and in w 0, or NaN
 // for a non-finite position (added in the list build's pre-test, which then
@@ -407,16 +415,12 @@ __device__ __forceinline__ float4 pack_fixed(const double *x3, const SysGeom &g)
 }
 
 // r_j - r_i from fixed-point positions (exact minimum image for |r| < L / 2).
-__device__ __forceinline__ void fixed_pair(const float4 &pj, const float4 &pi, const float fx[6], float &dx, float &dy,
+__device__ __forceinline__ void fixed_pair(const float4 &pj, const float4 &pi, const double fx[3], float &dx, float &dy,
                                            float &dz)
 {
-#pragma clang fp contract(off)
-    const float cx = (float)(int32_t)(__float_as_uint(pj.x) - __float_as_uint(pi.x));
-    const float cy = (float)(int32_t)(__float_as_uint(pj.y) - __float_as_uint(pi.y));
-    const float cz = (float)(int32_t)(__float_as_uint(pj.z) - __float_as_uint(pi.z));
-    dx = fmaf(cx, fx[0], cx * fx[3]);
-    dy = fmaf(cy, fx[1], cy * fx[4]);
-    dz = fmaf(cz, fx[2], cz * fx[5]);
+    dx = (float)((double)(int32_t)(__float_as_uint(pj.x) - __float_as_uint(pi.x)) * fx[0]);
+    dy = (float)((double)(int32_t)(__float_as_uint(pj.y) - __float_as_uint(pi.y)) * fx[1]);
+    dz = (float)((double)(int32_t)(__float_as_uint(pj.z) - __float_as_uint(pi.z)) * fx[2]);
 }
 
 // One packed position on the fine grid: per axis the fine cell c = floor(x / h) mod M

@@ -48,7 +48,7 @@ struct NepArgs {
 struct LaneMap {
     int i, b;        // atom and bead (clamped into range for idle lanes)
     bool valid;      // a real (atom, bead)
-    float fx[6];     // fixed-point quantum (high and low terms)
+    double fx[3];    // fixed-point quantum
     int M[3];
     float h[3];
     int form;        // PosForm of the tile's system
@@ -68,7 +68,6 @@ __device__ __forceinline__ LaneMap lane_map(const NepArgs &a, int thread)
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         m.fx[d] = g.fx[d];
-        m.fx[3 + d] = g.fx[3 + d];
         m.M[d] = g.M[d];
         m.h[d] = g.h[d];
     }
@@ -89,7 +88,6 @@ __device__ __forceinline__ LaneMap row_map(const SysGeom &g, int i, int b)
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         m.fx[d] = g.fx[d];
-        m.fx[3 + d] = g.fx[3 + d];
         m.M[d] = g.M[d];
         m.h[d] = g.h[d];
     }

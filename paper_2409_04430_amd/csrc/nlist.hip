@@ -963,8 +963,7 @@ int32_t update_geometry(const nep_model *m, nep_nlist *nl, const double *boxes, 
             g.hd[a] = fg.hd[a];
             g.Minv[a] = fg.Minv[a];
             g.h[a] = fg.h[a];
-            g.fx[a] = (float)(g.L[a] / 4294967296.0);
-            g.fx[3 + a] = (float)(g.L[a] / 4294967296.0 - (double)g.fx[a]);
+            g.fx[a] = g.L[a] / 4294967296.0;
             g.M[a] = fg.M[a];
             const int nc = (int)std::floor(ci.w[a] / (rc * (1.0 + 1e-9)));
             g.nc_cap[a] = nc < 1 ? 1 : (nc > 64 ? 64 : nc);
