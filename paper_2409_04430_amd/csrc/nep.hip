@@ -31,7 +31,7 @@ namespace nep {
 
 // ----------------------------------------------------------- pass 1 ---
 
-template <int NR1, int NA1, int KR1, int KA1, bool FOUR, int NET, bool FINE>
+template <int NR1, int NA1, int KR1, int KA1, bool FOUR, int NET, int FORM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_descriptor(NepArgs a, const float *__restrict__ prm)
 {
@@ -117,7 +117,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                 for (int u = 0; u < kBatchR; ++u) {
                     if (in[u]) {
                         float dx, dy, dz;
-                        pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
+                        pair_vec<FORM>(pj[u], pi, lm, dx, dy, dz);
                         const float r2 = norm2(dx, dy, dz);
                         {
                             // sk[0] collects f_c, sk[k > 0] collects f_c T_k
@@ -196,7 +196,7 @@ void k_descriptor(NepArgs a, const float *__restrict__ prm)
                 for (int u = 0; u < kBatch; ++u) {
                     if (!in[u]) continue;
                     float dx, dy, dz;
-                    pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
+                    pair_vec<FORM>(pj[u], pi, lm, dx, dy, dz);
                     const float r2 = norm2(dx, dy, dz);
                     const float rinv = __builtin_amdgcn_rsqf(r2);
                     const float r = r2 * rinv;
@@ -446,7 +446,7 @@ constexpr int kSplitWaves = kTwoPartRows / 64;
 template <int NA1> constexpr int kAngWaves() { return NA1 > 5 ? 1 : 2; }
 constexpr int kBatchRev = 8;   // reverse angular terms read together by the radial force kernel
 
-template <int NA1, int KA1, bool FOUR, bool PARKED, bool FINE, int SUM>
+template <int NA1, int KA1, bool FOUR, bool PARKED, int FORM, int SUM>
 __global__ __launch_bounds__(SUM == kSumLanes ? 2 * kBlock : kBlock) __attribute__((amdgpu_waves_per_eu(kAngWaves<NA1>())))
 void k_force_ang(NepArgs a, const float *__restrict__ prm)
 {
@@ -582,7 +582,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
                 const bool act = aq[u];
                 if (__ballot(act) == 0) continue;
                 float dx, dy, dz;
-                pair_vec<FINE>(pq[u], pi, lm, dx, dy, dz);
+                pair_vec<FORM>(pq[u], pi, lm, dx, dy, dz);
                 if (!act) {
                     dx = 1.0f;
                     dy = 0.0f;
@@ -678,7 +678,7 @@ void k_force_ang(NepArgs a, const float *__restrict__ prm)
 // bead-minor), then the reverse angular terms -dU_j/dr_ji that the angular
 // pass deposited at this atom's slots, then the angular own part.  Force and
 // per-atom virial sums are kept in FP64.
-template <int KR1, bool FINE>
+template <int KR1, int FORM>
 __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
 {
     const LaneMap lm = lane_map(a, threadIdx.x);
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
                 for (int u = 0; u < kBatch; ++u) {
                     if (in[u]) {
                         float dx, dy, dz;
-                        pair_vec<FINE>(pj[u], pi, lm, dx, dy, dz);
+                        pair_vec<FORM>(pj[u], pi, lm, dx, dy, dz);
                         const float w = radial_pair_w<KR1>(norm2(dx, dy, dz), a.rcRinv, ai, aj[u]);
                         const float qx = w * dx, qy = w * dy, qz = w * dz;
                         bx = fmaf(w, dx, bx); by = fmaf(w, dy, by); bz = fmaf(w, dz, bz);
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void k_force_rad(NepArgs a)
                 for (int u = 0; u < kBatchRev; ++u) {
                     if (!in[u]) continue;
                     float dx, dy, dz;
-                    pair_vec<FINE>(*row_at(p4b, uW[sb + u] >> 2, pstride), pi, lm, dx, dy, dz);
+                    pair_vec<FORM>(*row_at(p4b, uW[sb + u] >> 2, pstride), pi, lm, dx, dy, dz);
                     const float4 dd = d[u];
                     // reverse half of the per-atom split: +1/2 r_ij (x) dU_j/dr_ji
                     const float hx = 0.5f * dx, hy = 0.5f * dy, hz = 0.5f * dz;
@@ -833,7 +833,7 @@ __global__ __launch_bounds__(64) void k_reduce(PendingReduce r)
 constexpr size_t kNetLdsMax = 60 * 1024;   // bytes of LDS for the staged network weights
 
 // mlp: NEP_MLP_FP32 (vector units), NEP_MLP_BF16_MFMA or NEP_MLP_FP32_MFMA (matrix cores).
-template <int NR1, int NA1, bool FOUR, bool FINE>
+template <int NR1, int NA1, bool FOUR, int FORM>
 static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int64_t min_rows, int mlp,
                      bool lds_net, hipStream_t s)
 {
@@ -845,45 +845,46 @@ static void launch_t(const NepArgs &a, const float *prm, int nblk, int wpb, int6
         const size_t net = sizeof(float) * (size_t)a.S * a.H * (DP + 2);
         const size_t mf = sizeof(float) * (size_t)mf_lds_floats<D>() * wpb;
         if (mlp == NEP_MLP_BF16_MFMA)   // BF16 weights (the student)
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetBf16, FINE>), g, blk, mf, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetBf16, FORM>), g, blk, mf, s, a, prm);
         else if (mlp == NEP_MLP_FP32_MFMA)   // FP32 weights as three BF16 terms
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetMf32, FINE>), g, blk, mf, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetMf32, FORM>), g, blk, mf, s, a, prm);
         else if (lds_net && net <= kNetLdsMax)   // network weights staged in LDS
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetLds, FINE>), g, blk, net, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetLds, FORM>), g, blk, net, s, a, prm);
         else
-            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetGlobal, FINE>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_descriptor<NR1, NA1, 9, 9, FOUR, kNetGlobal, FORM>), g, blk, 0, s, a, prm);
     }
     {
         ProfScope ps_(K_FORCE_ANG, s);
         const bool parked = adj_parked(mlp == NEP_MLP_BF16_MFMA || mlp == NEP_MLP_FP32_MFMA, NA1);
         if constexpr (adj_parked(false, NA1)) {   // wide sets are always parked
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumWhole>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FORM, kSumWhole>), g, blk, 0, s, a, prm);
         } else if (two_parts(NA1, a.lg) && nblk * wpb <= kSplitWaves) {
             const dim3 b2(128 * wpb);
-            if (parked) hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumLanes>), g, b2, 0, s, a, prm);
-            else hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE, kSumLanes>), g, b2, 0, s, a, prm);
+            if (parked) hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FORM, kSumLanes>), g, b2, 0, s, a, prm);
+            else hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FORM, kSumLanes>), g, b2, 0, s, a, prm);
         } else if (two_parts(NA1, a.lg) && min_rows <= kTwoPartRows) {
-            if (parked) hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumParts>), g, blk, 0, s, a, prm);
-            else hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE, kSumParts>), g, blk, 0, s, a, prm);
+            if (parked) hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FORM, kSumParts>), g, blk, 0, s, a, prm);
+            else hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FORM, kSumParts>), g, blk, 0, s, a, prm);
         } else if (parked) {
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FINE, kSumWhole>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, true, FORM, kSumWhole>), g, blk, 0, s, a, prm);
         } else {
-            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FINE, kSumWhole>), g, blk, 0, s, a, prm);
+            hipLaunchKernelGGL((k_force_ang<NA1, 9, FOUR, false, FORM, kSumWhole>), g, blk, 0, s, a, prm);
         }
     }
     {
         ProfScope ps_(K_FORCE, s);
-        hipLaunchKernelGGL((k_force_rad<9, FINE>), g, blk, 0, s, a);
+        hipLaunchKernelGGL((k_force_rad<9, FORM>), g, blk, 0, s, a);
     }
 }
 
-// Lists with fixed-point positions and lists with fine-grid positions (general cells, long edges).
+// form: the list's (what the launch carries code for).
 template <int NR1, int NA1, bool FOUR>
-static void launch(const NepArgs &a, const float *prm, int nblk, int wpb, int64_t min_rows, bool fine, int mlp,
+static void launch(const NepArgs &a, const float *prm, int nblk, int wpb, int64_t min_rows, int form, int mlp,
                    bool lds_net, hipStream_t s)
 {
-    if (fine) launch_t<NR1, NA1, FOUR, true>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
-    else launch_t<NR1, NA1, FOUR, false>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
+    if (form == kPosFixed) launch_t<NR1, NA1, FOUR, kPosFixed>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
+    else if (form == kPosGrid) launch_t<NR1, NA1, FOUR, kPosGrid>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
+    else launch_t<NR1, NA1, FOUR, kPosAny>(a, prm, nblk, wpb, min_rows, mlp, lds_net, s);
 }
 
 }  // namespace nep
@@ -952,16 +953,15 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
         r.rowp = ws->rowp; r.tile_atom0 = ws->tile_atom0; r.tile_atom1 = ws->tile_atom1; r.N = N;
     } else {
         const int key = h.n_max_radial * 100 + h.n_max_angular * 10 + h.four_body;
-        const bool fine = nl->fine_pos != 0;
         int64_t min_rows = INT64_MAX;   // the smallest (non-empty) system
         for (int sy = 0; sy < nsys; ++sy)
             if (ws->off[sy + 1] > ws->off[sy]) min_rows = std::min(min_rows, (int64_t)P * (ws->off[sy + 1] - ws->off[sy]));
         switch (key) {
-        case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
-        case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
-        case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
-        case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
-        case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, min_rows, fine, mlp, !ws->net_global, s); break;
+        case 440: launch<5, 5, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, nl->form, mlp, !ws->net_global, s); break;
+        case 441: launch<5, 5, true>(a, m->dev, ws->nblk, ws->wpb, min_rows, nl->form, mlp, !ws->net_global, s); break;
+        case 640: launch<7, 5, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, nl->form, mlp, !ws->net_global, s); break;
+        case 860: launch<9, 7, false>(a, m->dev, ws->nblk, ws->wpb, min_rows, nl->form, mlp, !ws->net_global, s); break;
+        case 881: launch<9, 9, true>(a, m->dev, ws->nblk, ws->wpb, min_rows, nl->form, mlp, !ws->net_global, s); break;
         default: return fail(NEP_ERR_UNSUPPORTED, "nep_compute: unsupported model shape");
         }
         r.partE = ws->partE; r.partWa = a.partWa; r.partWr = a.partWr;

@@ -122,15 +122,14 @@ __device__ __forceinline__ void block_range(const int32_t *uend, int i, int t, i
     s1 = uend[(size_t)i * kMaxSpecies + t];
 }
 
-// Pair vector r_j - r_i from packed positions.  FINE = false: every system
-// of the launch has fixed-point positions; otherwise each tile takes its
-// system's form (a uniform branch).
-template <bool FINE>
+// Pair vector r_j - r_i from packed positions; FORM: the launch's form
+// (kPosAny: each tile takes its system's by a uniform branch).
+template <int FORM>
 __device__ __forceinline__ void pair_vec(const float4 &pj, const float4 &pi, const LaneMap &lm, float &dx, float &dy,
                                          float &dz)
 {
-    if (!FINE || lm.form == kPosFixed) fixed_pair(pj, pi, lm.fx, dx, dy, dz);
-    else if (lm.form == kPosGridTri) packed_pair_tri(pj, pi, lm.M, lm.hv, dx, dy, dz);
+    if (FORM == kPosFixed || (FORM == kPosAny && lm.form == kPosFixed)) fixed_pair(pj, pi, lm.fx, dx, dy, dz);
+    else if (FORM == kPosAny && lm.form == kPosGridTri) packed_pair_tri(pj, pi, lm.M, lm.hv, dx, dy, dz);
     else packed_pair(pj, pi, lm.M, lm.h, dx, dy, dz);
 }
 

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
             for (int k = 0; k < KR1; ++k) T[k] = 0.0f;
             if (e < n && ((mR[e] >> b) & 1u)) {
                 float dx, dy, dz;
-                pair_vec<true>(*row_at(p4b, uR[e], pstride), pi, lm, dx, dy, dz);
+                pair_vec<kPosAny>(*row_at(p4b, uR[e], pstride), pi, lm, dx, dy, dz);
                 cheb_t<KR1>(__builtin_amdgcn_sqrtf(norm2(dx, dy, dz)), a.rcRinv, fc, T);
             }
             sy[lane * kYPad] = fc;
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
             if (e < nA && ((mA[e] >> b) & 1u)) {
                 const int32_t w = uW[e];
                 float dx, dy, dz;
-                pair_vec<true>(*row_at(p4b, w >> 2, pstride), pi, lm, dx, dy, dz);
+                pair_vec<kPosAny>(*row_at(p4b, w >> 2, pstride), pi, lm, dx, dy, dz);
                 const float r2 = norm2(dx, dy, dz);
                 const float rinv = __builtin_amdgcn_rsqf(r2);
                 const float r = r2 * rinv;
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(64) void k_small_site(NepArgs a, const float *__res
         if (act) {
             const int32_t w = uW[e];
             const int rk = uV[e], j = w >> 2, t = w & 3;
-            pair_vec<true>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
+            pair_vec<kPosAny>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
             const float r2 = norm2(dx, dy, dz);
             const float rinv = __builtin_amdgcn_rsqf(r2);
             const float r = r2 * rinv;
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(64) void k_small_rad(NepArgs a, const int32_t *__re
                     const int j = uR[e];
                     float aj[KR1 + 1];
                     load_a(row_at(abt, j, astride), aj);
-                    pair_vec<true>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
+                    pair_vec<kPosAny>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
                     w = radial_pair_w<KR1>(norm2(dx, dy, dz), a.rcRinv, ai, aj);
                 }
                 float *o = sv + lane * kPad;
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(64) void k_small_rad(NepArgs a, const int32_t *__re
             if (e < nA && ((mA[e] >> b) & 1u)) {
                 const int slot = uA[e];
                 d = *row_at(pbuf, slot, pstride);
-                if (a.Watom) pair_vec<true>(*row_at(p4b, uW[e] >> 2, pstride), pi, lm, dx, dy, dz);
+                if (a.Watom) pair_vec<kPosAny>(*row_at(p4b, uW[e] >> 2, pstride), pi, lm, dx, dy, dz);
             }
             float *o = sv + lane * kPad;
             o[0] = d.x; o[1] = d.y; o[2] = d.z;

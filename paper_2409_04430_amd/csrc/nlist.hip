@@ -693,9 +693,8 @@ constexpr double kShellEps = 1e-3;   // A; far above the rounding of d and s
 constexpr int kRevRows = 4;          // partners' rows whose loads are in flight together
 constexpr int kUnionRounds = 4;      // shell rounds whose partner loads are in flight together
 
-// FINE: fine-grid positions, general cells possible; otherwise fixed-point
-// positions of orthorhombic cells, with no general-cell code.
-template <bool FINE>
+// FORM: the launch's positions (kPosAny: general cells possible).
+template <int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_union(const double *__restrict__ pos, const float4 *__restrict__ pos4,
                                                const double *__restrict__ cen, const float *__restrict__ spr,
                                                const float4 *__restrict__ cen4, int P,
@@ -777,7 +776,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const float4 pi = pos4[(size_t)i * P + bb];
     const double *pb = pos + (size_t)bb * N * 3;
     const SysGeom &g = geom[atom_sys[i]];
-    const bool tri = FINE && g.tri;
+    const bool tri = FORM == kPosAny && g.tri;   // the other launches carry no general-cell code
     const uint64_t gmask = (G == 64) ? ~0ull : ((1ull << G) - 1ull);
     const uint64_t full = (P == 64) ? ~0ull : ((1ull << P) - 1ull);
 
@@ -805,7 +804,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const int rv = kind && kin ? revA[(size_t)i * cap + k] : 0;
             // d + s < rc - eps and d - s > rc + eps, on squares
             bool all_in, out;
-            if (FINE) {
+            if (FORM != kPosFixed) {
                 double dv[3];
 #pragma unroll
                 for (int d = 0; d < 3; ++d) dv[d] = cen[3 * (size_t)j + d] - cen[3 * (size_t)i + d];
@@ -845,7 +844,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 for (int u = 0; u < kUnionRounds; ++u) pj[u] = pos4[(size_t)jq[u] * P + bb];
 #pragma unroll
                 for (int u = 0; u < kUnionRounds; ++u) {
-                    const float r2f = packed_r2<FINE>(pj[u], pi, g);
+                    const float r2f = packed_r2<FORM>(pj[u], pi, g);
                     const bool in = (u0 + u) * CPW + cg < ns && bead_ok && pair_within(r2f, c, pb, i, jq[u], g, tri);
                     const uint64_t m = (__ballot(in) >> ((lane & (CPW - 1)) << lg)) & gmask;
                     if (lane >> (6 - lg) == u0 + u) {
@@ -912,7 +911,7 @@ __global__ __launch_bounds__(256) void k_materialize(const double *__restrict__ 
         int cnt = 0;
         for (int k = 0; k < n; ++k) {
             const int j = row[k] >> 2;
-            if (pair_within(packed_r2<true>(pos4[(size_t)j * P + b], pi, g), c, pb, i, j, g, g.tri)) {
+            if (pair_within(packed_r2<kPosAny>(pos4[(size_t)j * P + b], pi, g), c, pb, i, j, g, g.tri)) {
                 if (cnt < out) nb[(size_t)cnt * N] = j;
                 ++cnt;
             }
@@ -994,10 +993,10 @@ int32_t update_geometry(const nep_model *m, nep_nlist *nl, const double *boxes, 
     margin = (float)(1e-3 * std::max(1.0, hmax * hmax) * std::max(1.0, rc * rc / 36.0));
     nl->margin = margin;
     nl->any_tri = 0;
-    nl->fine_pos = 0;
+    nl->form = nl->nsys ? G[0].form : kPosFixed;
     for (int s = 0; s < nl->nsys; ++s) {
         nl->any_tri |= G[s].tri;
-        nl->fine_pos |= G[s].form != kPosFixed;
+        if (G[s].form != nl->form) nl->form = kPosAny;
     }
     if (!changed) return NEP_OK;
     if (cell_total > nl->ncell_alloc) {
@@ -1071,7 +1070,7 @@ extern "C" int32_t neighbor_build_batched(const nep_model *m, nep_nlist *nl, con
         const double rR2 = m->hp.rc_radial * m->hp.rc_radial, rA2 = m->hp.rc_angular * m->hp.rc_angular;
         const CutTest cR{(float)rR2, margin, rR2};
         const CutTest cA{(float)rA2, margin, rA2};
-        auto kern = nl->fine_pos ? k_union<true> : k_union<false>;
+        auto kern = nl->form == kPosFixed ? k_union<kPosFixed> : nl->form == kPosGrid ? k_union<kPosGrid> : k_union<kPosAny>;
         hipLaunchKernelGGL(kern, dim3(div_up(N, kBlock / 64), 2), dim3(kBlock), 0, s, pos,
                            reinterpret_cast<const float4 *>(nl->pos4), nl->cen, nl->spr,
                            reinterpret_cast<const float4 *>(nl->cen4), P, N, nl->S, lg, nl->atom_sys, nl->geom, cR, cA,

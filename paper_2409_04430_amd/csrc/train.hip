@@ -186,7 +186,7 @@ void k_train_row(NepArgs a, TrainArgs ta, const float *__restrict__ prm, const i
                 const int j = uR[e];
                 const float4 dj = *row_at(dFb, j, pstride);
                 float dx, dy, dz, ex, ey, ez;
-                pair_vec<true>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
+                pair_vec<kPosAny>(*row_at(p4b, j, pstride), pi, lm, dx, dy, dz);
                 const float r2 = norm2(dx, dy, dz);
                 const float rinv = __builtin_amdgcn_rsqf(r2);
                 field(dj, dx, dy, dz, ex, ey, ez);
@@ -270,7 +270,7 @@ void k_train_row(NepArgs a, TrainArgs ta, const float *__restrict__ prm, const i
             tj = w & 3;
             const float4 dj = *row_at(dFb, w >> 2, pstride);
             float dx, dy, dz, ex, ey, ez;
-            pair_vec<true>(*row_at(p4b, w >> 2, pstride), pi, lm, dx, dy, dz);
+            pair_vec<kPosAny>(*row_at(p4b, w >> 2, pstride), pi, lm, dx, dy, dz);
             const float r2 = norm2(dx, dy, dz);
             const float rinv = __builtin_amdgcn_rsqf(r2);
             const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
