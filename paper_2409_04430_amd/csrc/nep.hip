@@ -946,7 +946,7 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     const int mlp = m->mlp;
     PendingReduce r;
     r.sys_tile0 = ws->sys_tile0; r.P = P; r.nblk = ws->nblk; r.nout = nsys * P * 10; r.E = E; r.W = W;
-    const bool small = ws->rowp && takes_small((int64_t)P * N, mlp);
+    const bool small = ws->rowp && takes_small((int64_t)P * N, P, h, nl->capR + nl->capA, mlp);
     if (small) {   // one wavefront per (atom, bead)
         const int32_t rcs = launch_small(a, m, nl->atom_sys, ws->rowp, s);
         if (rcs != NEP_OK) return rcs;
