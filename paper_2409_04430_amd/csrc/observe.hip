@@ -45,12 +45,9 @@ static int32_t rdf_scratch(int dev, double **out)
     return NEP_OK;
 }
 
-constexpr int kRdfLanes = 128;        // (atom, bead) lanes of a workgroup's turn
-constexpr int kRdfParts = 8;          // threads that share a lane's list
-constexpr int kRdfBlock = kRdfLanes * kRdfParts;
 constexpr int kRdfMaxWords = 16384;   // S * S * nbins bins of 32-bit counts in LDS (64 KB)
-constexpr int kRdfMaxGroups = 256;
 constexpr int kRdfBatch = 8;
+constexpr int64_t kRdfManyLanes = 131072;   // a turn of 512 workgroups with 256 lanes each
 
 // Bead-minor copy of the positions, [N][P][3]: the beads of a neighbour are
 // then one contiguous run for the lanes that gather them.
@@ -67,28 +64,37 @@ __global__ void k_beads_minor(const double *__restrict__ pos, double *__restrict
 }
 
 // One lane per (atom, bead) in a grid-stride loop, the beads of an atom in
-// G = 2^lg adjacent lanes, and kRdfParts threads (of different wavefronts)
-// per lane, which take its atom's radial union list in turns of a batch: one
+// G = 2^lg adjacent lanes, and PARTS threads (of different wavefronts) per
+// lane, which take its atom's radial union list in turns of a batch: one
 // thread per lane left 1.5 wavefronts on a SIMD at 3072 atoms x 32 beads, which
 // spent 59 % of their time waiting, and the counts do not depend on their
-// order.  The whole observables call: 86 us with one thread per lane, 62 with
-// four and 384 workgroups, 55 with eight and one workgroup per compute unit,
-// whose histograms meet in fewer global atomics (192 workgroups: 63).  A batch's loads are in flight together; the
-// thread keeps the entries whose bead
-// mask holds its bead, and counts the pair's bin in the workgroup's LDS
-// histogram; the workgroup then adds its non-zero bins to the global 64-bit
-// histogram.  Orthorhombic cells: the image shift is rint(x (1/L)); every
-// listed pair is closer than the cutoff, far from the half-integer points
-// where it could differ from rint(x / L), so the distance is the same double
-// as with the division.  General cells: the fractional difference reduced by
-// rint and mapped back, in the same order of operations as the list test.
+// order.  The whole observables call there: 86 us with one thread per lane, 62
+// with four and 384 workgroups, 55 with eight and one workgroup per compute
+// unit, whose histograms meet in fewer global atomics (192 workgroups: 63).
+// Launches with lanes to spare (kRdfManyLanes) take two threads per lane:
+// with eight, most of them find no batch of a short list and repeat the
+// lane's loads.  One histogram call, us by one / eight / two: a four-species
+// framework with about 11 neighbours 30000 atoms x 32 beads 96 / 155 / 83,
+// 20000 x 16 44 / 59 / 38; FCC metal 30000 x 32 255 / 240 / 197; water
+// 20000 x 16 135 / 106 / 96; fewer lanes: metal 60000 x 1 52 / 44 / 45,
+// water 60000 x 1 75 / 59 / 66.  A batch's loads are in flight together; the
+// thread keeps the entries whose bead mask holds its bead, and counts the
+// pair's bin in the workgroup's LDS histogram; the workgroup then adds its
+// non-zero bins to the global 64-bit histogram.  Orthorhombic cells: the
+// image shift is rint(x (1/L)); every listed pair is closer than the cutoff,
+// far from the half-integer points where it could differ from rint(x / L), so
+// the distance is the same double as with the division.  General cells: the
+// fractional difference reduced by rint and mapped back, in the same order of
+// operations as the list test.
 struct RdfCell {
     double L[3], iL[3];     // orthorhombic: edges and their inverses
     double H[9], G[9];      // general: edge vectors as rows and H^-1
     int tri;
 };
 
-__global__ __launch_bounds__(kRdfBlock) void k_rdf(const double *__restrict__ posT, const int32_t *__restrict__ types,
+// LANES: (atom, bead) lanes of a workgroup's turn; PARTS: threads that share a lane's list.
+template <int LANES, int PARTS>
+__global__ __launch_bounds__(LANES * PARTS) void k_rdf(const double *__restrict__ posT, const int32_t *__restrict__ types,
                                                    int P, int N, int S, int lg, RdfCell cell,
                                                    double inv, int nbins, const int32_t *__restrict__ uni,
                                                    const uint64_t *__restrict__ um, const int32_t *__restrict__ uend,
@@ -100,9 +106,9 @@ __global__ __launch_bounds__(kRdfBlock) void k_rdf(const double *__restrict__ po
     __syncthreads();
     const int G = 1 << lg;
     const int64_t lanes = (int64_t)N << lg;
-    const int part = threadIdx.x / kRdfLanes;   // wave-uniform
-    for (int64_t t = (int64_t)blockIdx.x * kRdfLanes + threadIdx.x % kRdfLanes; t < lanes;
-         t += (int64_t)gridDim.x * kRdfLanes) {
+    const int part = threadIdx.x / LANES;   // wave-uniform
+    for (int64_t t = (int64_t)blockIdx.x * LANES + threadIdx.x % LANES; t < lanes;
+         t += (int64_t)gridDim.x * LANES) {
         const int i = (int)(t >> lg), b = (int)(t & (G - 1));
         if (b >= P) continue;
         const int ti = types[i];
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(kRdfBlock) void k_rdf(const double *__restrict__ po
             const int s1 = uend[(size_t)i * kMaxSpecies + tt];
             const int base = (ti * S + tt) * nbins;
             const int nb = (s1 - s0 + kRdfBatch - 1) / kRdfBatch;
-            for (; turn < nb; turn += kRdfParts) {
+            for (; turn < nb; turn += PARTS) {
                 const int sb = s0 + turn * kRdfBatch;
                 int jj[kRdfBatch];
                 bool in[kRdfBatch];
@@ -213,7 +219,6 @@ static int32_t rdf_accumulate(const nep_model *m, nep_nlist *nl, const double *p
     int lg = 0;
     while ((1 << lg) < P) ++lg;
     const int64_t lanes = (int64_t)N << lg;
-    const int groups = (int)std::min<int64_t>((lanes + kRdfLanes - 1) / kRdfLanes, kRdfMaxGroups);
     const size_t lds = sizeof(uint32_t) * (size_t)S * S * nbins;
     const bool own = !posT;   // the library's own copy; timed when kernel timing is on
     if (own) {
@@ -234,8 +239,12 @@ static int32_t rdf_accumulate(const nep_model *m, nep_nlist *nl, const double *p
         cell.L[a] = ci.H[4 * a];
         cell.iL[a] = 1.0 / ci.H[4 * a];
     }
-    hipLaunchKernelGGL(k_rdf, dim3(groups), dim3(kRdfBlock), lds, s, posT, types, P, N, S, lg, cell, nbins / rmax,
-                       nbins, nl->uniR, nl->umR, nl->uendR, nl->capR, reinterpret_cast<unsigned long long *>(hist));
+    const bool many = lanes > kRdfManyLanes;
+    const int turn = many ? 256 : 128, block = many ? 512 : 1024, most = many ? 512 : 256;   // as in the variants
+    const int groups = (int)std::min<int64_t>((lanes + turn - 1) / turn, most);
+    hipLaunchKernelGGL((many ? k_rdf<256, 2> : k_rdf<128, 8>), dim3(groups), dim3(block), lds, s, posT, types, P, N, S,
+                       lg, cell, nbins / rmax, nbins, nl->uniR, nl->umR, nl->uendR, nl->capR,
+                       reinterpret_cast<unsigned long long *>(hist));
     NEP_HIP(hipGetLastError());
     return NEP_OK;
 }
