@@ -926,7 +926,7 @@ extern "C" int32_t nep_compute_batched(const nep_model *m, nep_nlist *nl, nep_ws
     const nep_hparams &h = m->hp;
     NepArgs a{};
     // packed positions of the last neighbor_build (the same positions, see the header)
-    a.p4 = reinterpret_cast<const float4 *>(nl->pos4); a.pos = pos; a.types = types; a.N = N; a.S = h.n_species;
+    a.p4 = reinterpret_cast<const float4 *>(nl->pos4); a.types = types; a.N = N; a.S = h.n_species;
     a.H = h.hidden; a.P = P; a.lg = lanes_log2(P);
     a.geom = nl->geom; a.tile_atom0 = ws->tile_atom0; a.tile_atom1 = ws->tile_atom1; a.tile_sys = ws->tile_sys; a.sys_tile0 = ws->sys_tile0;
     a.rcRinv = (float)(1.0 / h.rc_radial); a.rcAinv = (float)(1.0 / h.rc_angular);

@@ -12,7 +12,6 @@ constexpr int kRadPad = 12;   // padded length of a radial adjoint row (float4 a
 
 struct NepArgs {
     const float4 *p4;    // [N][P] packed positions (bead-minor)
-    const double *pos;   // [P][N][3] FP64 positions (exact test near the cutoff)
     const int32_t *types;
     int N, S, H, P, lg;  // lg: log2 of the lanes per atom
     const SysGeom *geom; // per system: fine grid of the packed positions

@@ -807,12 +807,11 @@ extern "C" int32_t nep_param_grad_batched(const nep_model *m, nep_nlist *nl, nep
                        tw->dF, tw->cW, tw->eE, tw->lossp, tw->nfblk);
     const nep_hparams &h = m->hp;
     NepArgs a{};
-    a.p4 = reinterpret_cast<const float4 *>(nl->pos4); a.pos = pos; a.types = types; a.N = N; a.S = h.n_species;
-    a.H = h.hidden; a.P = P; a.lg = lanes_log2(P);
-    a.geom = nl->geom; a.tile_atom0 = ws->tile_atom0; a.tile_atom1 = ws->tile_atom1; a.tile_sys = ws->tile_sys;
+    a.p4 = reinterpret_cast<const float4 *>(nl->pos4); a.types = types; a.N = N; a.S = h.n_species;
+    a.H = h.hidden; a.P = P;
+    a.geom = nl->geom;
     a.rcRinv = (float)(1.0 / h.rc_radial); a.rcAinv = (float)(1.0 / h.rc_angular);
-    a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniA = nl->uniA;
-    a.uniW = nl->uniW; a.uniV = nl->uniV;
+    a.uniR = nl->uniR; a.uendR = nl->uendR; a.uniW = nl->uniW;
     a.umR = nl->umR; a.umA = nl->umA; a.uendA = nl->uendA; a.capR = nl->capR; a.capA = nl->capA;
     a.oR = m->off.cR; a.oA = m->off.cA; a.oq = m->off.qs; a.oW0 = m->off.W0; a.ob0 = m->off.b0;
     a.ow1 = m->off.w1; a.ob1 = m->off.b1; a.osh = m->off.sh;
