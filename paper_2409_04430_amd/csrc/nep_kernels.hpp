@@ -215,8 +215,9 @@ constexpr int gad_q(int NA1, bool four) { return NA1 + (four ? (NA1 + 3) / 4 : 0
 // store reads its data registers over several cycles, and the compiler keeps
 // the next instructions from overwriting them only where the scalar offset is
 // a constant.  With the offset there, a vector instruction directly behind
-// the store replaced the last four lanes of each sixteen in about 3 % of the
-// descriptor launches of a 9 + 9 radial function model (32000 atoms x 32).
+// the store replaced the last four lanes of each sixteen of one wavefront in
+// 22 of 150 descriptor launches of a 9 + 9 radial function model (32000 atoms
+// x 32; 0 of 400 as it stands).
 __device__ __forceinline__ void adj_store(__amdgpu_buffer_rsrc_t r, int q, float4 v)
 {
     const u32x4_t u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};

@@ -671,8 +671,8 @@ __global__ __launch_bounds__(256) void k_candidates(const double *__restrict__ c
 // the two atoms' largest bead distances from their centroids, every bead
 // pair lies within [d - s, d + s] (the minimum image is the shortest image),
 // so d + s < rc - eps keeps all beads and d - s > rc + eps none (d is the
-// nearest-image distance, also in general cells: mic_vec; in orthorhombic
-// cells d and s come from one 16-byte record per candidate, the centroid in
+// nearest-image distance, also in general cells: mic_vec; for fixed-point
+// positions d and s come from one 16-byte record per candidate, the centroid in
 // the fixed-point form and the spread: the gathers are bound by the address
 // rate, one cache line per candidate and load).  Only the
 // remaining shell candidates are tested bead by bead (the exact test of the
@@ -683,13 +683,18 @@ __global__ __launch_bounds__(256) void k_candidates(const double *__restrict__ c
 // the mask of its own rank, so a round costs the same at every bead count
 // (found one after another by their bit positions, with a store of each mask,
 // they took 64 / G serial steps a round).  Per call: 16 water boxes of 192 to
-// 3072 atoms x 32 beads 194 -> 95 us, 4608 water atoms 39 -> 27 us, 4096
-// atoms x 32 beads 20.5 -> 12.6 us, 32000 x 32 116 -> 63 us.
+// 3072 atoms x 32 beads 194 -> 95 us, 1536 water atoms 39 -> 27 us (10 with
+// the status slots), 4096 atoms x 32 beads 20.5 -> 12.6 us, 32000 x 32 116 ->
+// 63 us.
 // Writing the angular entries' words and reverse slots as well takes 10 to
 // 12 us of the two large cases and saves the force kernels a dependent gather
 // per entry: 32000 x 32 with nine radial functions 3145 -> 3043 us in all,
 // the water boxes 1492 -> 1476 us, 16384 x 16 with five 474 -> 456 us.
-constexpr double kShellEps = 1e-3;   // A; far above the rounding of d and s
+//
+// The band kShellEps (A) lies far above the rounding of d and s, which are FP32
+// for fixed-point positions: where they decide, both are below 200 A and off by
+// less than 5e-5 A, so a pair that rounding could move is tested exactly.
+constexpr double kShellEps = 1e-3;
 constexpr int kRevRows = 4;          // partners' rows whose loads are in flight together
 constexpr int kUnionRounds = 4;      // shell rounds whose partner loads are in flight together
 
