@@ -115,10 +115,11 @@ __global__ __launch_bounds__(256) void k_residual(const float *__restrict__ F, c
 // A lane per row instead walked the angular neighbours once for every two
 // radial functions and once more for every coefficient row: 560 us for eight
 // 256-atom snapshots of 32 beads (65,536 rows, one wavefront per SIMD) and as
-// long for a single small snapshot; this kernel takes 417 us there (three
-// wavefronts per SIMD; at two 476) and falls with the rows.  The sums as
-// 16 x 16 x 4 FP32 matrix-core tiles (mostly padding at 5 functions and 24
-// harmonics) measured slower, 427 us.
+// long for a single small snapshot; this kernel took 417 us there (three
+// wavefronts per SIMD; at two 476), 375 since pair vectors are FP64 products,
+// and falls with the rows.  The sums as 16 x 16 x 4 FP32 matrix-core tiles
+// (mostly padding at 5 functions and 24 harmonics) measured slower, 427 us
+// against the 417.
 constexpr int kRowStage = 32;   // neighbours staged at a time (LDS)
 template <int NR1, int NA1>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
